@@ -8,6 +8,9 @@ from __future__ import annotations
 
 import ctypes
 import os
+import threading
+import weakref
+from collections import OrderedDict
 from typing import Optional, Tuple
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -212,9 +215,14 @@ def cvx_conv_fwd_query(xd, wd, conv, yd) -> Tuple[str, int]:
 
 
 # ---- torch-tensor convenience layer (still marshalling only) -----------------------------------
+_TORCH_DTYPE_CODES = {}
+
+
 def _torch_dtype_code(t) -> int:
-    import torch
-    return {torch.float32: CVX_F32, torch.float16: CVX_F16, torch.bfloat16: CVX_BF16}[t.dtype]
+    if not _TORCH_DTYPE_CODES:
+        import torch
+        _TORCH_DTYPE_CODES.update({torch.float32: CVX_F32, torch.float16: CVX_F16, torch.bfloat16: CVX_BF16})
+    return _TORCH_DTYPE_CODES[t.dtype]
 
 
 def _pair(v) -> Tuple[int, int]:
@@ -283,6 +291,44 @@ class ConvPlan:
         self.close()
 
 
+class _PlanCache:
+    """Plans the one-call function keeps between calls, one cache per thread (a handle serves one thread at a time).
+
+    Making a plan (a handle, five descriptors, the kernel search, and giving them back) is about ten times the
+    host work of the launch itself, so calls that repeat a problem reuse it.  The key is the whole problem
+    and the device and stream it runs on; nothing of the data is kept.  Bounded: the plan unused for longest is
+    closed when a new one would be the seventeenth; a thread's plans are closed when it ends."""
+    LIMIT = 16
+
+    def __init__(self):
+        self.plans = OrderedDict()
+        weakref.finalize(self, self._close, self.plans)
+
+    def get(self, key, args) -> ConvPlan:
+        plan = self.plans.get(key)
+        if plan is None:
+            plan = ConvPlan(*args)
+            if len(self.plans) >= self.LIMIT:
+                self.plans.popitem(last=False)[1].close()
+            self.plans[key] = plan
+        else:
+            self.plans.move_to_end(key)
+        return plan
+
+    @staticmethod
+    def _close(plans) -> None:
+        for plan in plans.values():
+            plan.close()
+
+
+class _PerThread(threading.local):
+    def __init__(self):
+        self.plans = _PlanCache()      # dropped, and with it its plans, when the thread ends
+
+
+_per_thread = _PerThread()
+
+
 def conv_fwd_fused(x, w, bias=None, *, pad=0, stride=1, dil=1, groups=1, act=CVX_ACT_RELU, alpha=0.0,
                    bn=None, eps=1e-5, out=None, policy: int = 0, pin: Optional[str] = None,
                    info: Optional[dict] = None):
@@ -296,18 +342,27 @@ def conv_fwd_fused(x, w, bias=None, *, pad=0, stride=1, dil=1, groups=1, act=CVX
     if not (x.is_contiguous() and w.is_contiguous()):
         raise ValueError("tensors must be contiguous (packed NCHW / KCRS)")
     dt = _torch_dtype_code(x)
-    stream = torch.cuda.current_stream(x.device).cuda_stream
+    device = x.get_device()
+    hip_stream = torch._C._cuda_getCurrentRawStream(device)
     bias_dt = None if bias is None else _torch_dtype_code(bias)
     if bias is not None and not (bias.is_cuda and bias.is_contiguous()):
         raise ValueError("bias must be a contiguous GPU tensor")
     bias_ch = None if bias is None else bias.numel()
-    with ConvPlan(dt, tuple(x.shape), tuple(w.shape), pad, stride, dil, groups, bias_dt, stream, bias_ch) as plan:
-        cvx_set_kernel_policy(plan.h, policy)
-        if pin:
+    args = (dt, tuple(x.shape), tuple(w.shape), _pair(pad), _pair(stride), _pair(dil), groups, bias_dt, hip_stream, bias_ch)
+    if pin or policy:
+        plan = ConvPlan(*args)          # developer choices of a kernel are for this call alone
+    else:
+        plan = _per_thread.plans.get((device,) + args, args)
+    try:
+        if pin or policy:
+            cvx_set_kernel_policy(plan.h, policy)
             plan.pin(pin)
-        y = out if out is not None else torch.empty(plan.y_shape, dtype=x.dtype, device=x.device)
-        if tuple(y.shape) != tuple(plan.y_shape) or not y.is_contiguous() or y.dtype != x.dtype:
-            raise ValueError("out has the wrong shape, dtype or layout")
+        if out is None:
+            y = torch.empty(plan.y_shape, dtype=x.dtype, device=x.device)
+        else:
+            y = out
+            if tuple(y.shape) != tuple(plan.y_shape) or not y.is_contiguous() or y.dtype != x.dtype:
+                raise ValueError("out has the wrong shape, dtype or layout")
         bp = None if bias is None else bias.data_ptr()
         if bn is None:
             plan.run(x.data_ptr(), w.data_ptr(), bp, y.data_ptr(), act, alpha)
@@ -317,4 +372,7 @@ def conv_fwd_fused(x, w, bias=None, *, pad=0, stride=1, dil=1, groups=1, act=CVX
                         eps, y.data_ptr(), act, alpha)
         if info is not None:
             info["kernel"] = plan.last_kernel()
+    finally:
+        if pin or policy:
+            plan.close()
     return y
