@@ -214,9 +214,11 @@ bool make_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out)
             if (strncmp(env.pin, "stem_", 5) == 0) return stem_plan(a, env, out);
             if (strncmp(env.pin, "igemm_", 6) == 0) return igemm_plan(a, env, out);
             if (strncmp(env.pin, "tiled_f32_", 10) == 0) return tiled_f32_plan(a, env, out);
+            if (strncmp(env.pin, "grouped_", 8) == 0) return grouped_plan(a, env, out);
             if (strncmp(env.pin, "direct", 6) == 0) return direct_plan(a, env, out);
             return false;
         }
+        if (a.groups > 1 && grouped_plan(a, env, out)) return true;
         if (pointwise_plan(a, env, out)) return true;
         if (stem_plan(a, env, out)) return true;
         if (igemm_plan(a, env, out)) return true;
@@ -231,6 +233,7 @@ hipError_t launch_plan(const ConvArgs& a, const LaunchPlan& p, hipStream_t s)
     case KID_IGEMM:     return igemm_launch(a, p, s);
     case KID_STEM:      return stem_launch(a, p, s);
     case KID_POINTWISE: return pointwise_launch(a, p, s);
+    case KID_GROUPED:   return grouped_launch(a, p, s);
     case KID_TILED_F32: return tiled_f32_launch(a, p, s);
     default:            return direct_launch(a, p, s);
     }

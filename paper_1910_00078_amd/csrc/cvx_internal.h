@@ -9,6 +9,27 @@ namespace cvx {
 enum : int { DT_F32 = 0, DT_F16 = 1, DT_BF16 = 2 };
 enum : int { ACT_IDENTITY = 0, ACT_RELU = 1, ACT_LEAKY_RELU = 2, ACT_TANH = 3, ACT_LOGISTIC = 4 };
 
+// Division of a non-negative 31-bit integer by a divisor fixed on the host: q = n / d with one multiply-high and
+// a shift (m = floor(2^(31 + l) / d) + 1 with l = ceil(log2 d); exact for every n < 2^31).
+struct Div31 {
+    uint32_t m;
+    int shift;                // l - 1; -1: d is 1
+    __host__ __device__ int div(int n) const
+    {
+        if (shift < 0) return n;
+        return (int)((uint32_t)(((unsigned long long)(uint32_t)n * m) >> 32) >> shift);
+    }
+};
+inline Div31 div31(int d)
+{
+    int l = 0;
+    while ((1LL << l) < d) ++l;
+    Div31 r;
+    r.m = l ? (uint32_t)((1ull << (31 + l)) / (uint32_t)d + 1) : 0u;
+    r.shift = l - 1;
+    return r;
+}
+
 // Everything a kernel needs to know about one forward convolution.  Plain data, passed by value.
 struct ConvArgs {
     const void* x;
@@ -35,6 +56,7 @@ enum KernelId : int {
     KID_STEM,                // low-channel strided direct-MFMA kernel
     KID_POINTWISE,           // persistent streaming kernel for 1x1 filters
     KID_TILED_F32,           // LDS-tiled fp32 kernel on the fp32 matrix instruction
+    KID_GROUPED,             // register-tiled kernel for few channels per group
     KID_COUNT
 };
 
@@ -66,6 +88,8 @@ bool pointwise_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out);
 hipError_t pointwise_launch(const ConvArgs& a, const LaunchPlan& p, hipStream_t s);
 bool tiled_f32_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out);
 hipError_t tiled_f32_launch(const ConvArgs& a, const LaunchPlan& p, hipStream_t s);
+bool grouped_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out);
+hipError_t grouped_launch(const ConvArgs& a, const LaunchPlan& p, hipStream_t s);
 bool direct_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out);
 hipError_t direct_launch(const ConvArgs& a, const LaunchPlan& p, hipStream_t s);
 
