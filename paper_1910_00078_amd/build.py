@@ -18,6 +18,9 @@ OBJ = os.path.join(CSRC, "_obj")
 LIB = os.path.join(HERE, "libcvx.so")
 SOURCES = ["cvx_api.cpp", "kernels_direct.hip", "kernels_igemm.hip", "kernels_stem.hip", "kernels_pointwise.hip",
            "kernels_tiled_f32.hip", "kernels_grouped.hip"]
+# Sources whose kernels are dealt over further objects (the same file with -DCVX_PART=1..n), so that a build uses the
+# machine's cores: one kernel of the implicit-GEMM family takes the compiler about ten seconds.
+PARTS = {"kernels_igemm.hip": 6}
 HEADERS = ["cvx_internal.h", "cvx_device.h", os.path.join("..", "..", "include", "cvx.h")]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
@@ -59,10 +62,12 @@ def _build(force, verbose, defines, LIB, OBJ) -> str:
     objs = []
     for src in SOURCES:
         s = os.path.join(CSRC, src)
-        o = os.path.join(OBJ, os.path.splitext(src)[0] + ".o")
-        objs.append(o)
-        if force or _stale(o, [s] + hdrs):
-            jobs.append([hipcc, "-x", "hip", "-c", s, "-o", o] + FLAGS + ["-D" + d for d in defines])
+        for part in range(PARTS.get(src, 0), -1, -1):
+            o = os.path.join(OBJ, os.path.splitext(src)[0] + (".%d.o" % part if part else ".o"))
+            objs.append(o)
+            if force or _stale(o, [s] + hdrs):
+                jobs.append([hipcc, "-x", "hip", "-c", s, "-o", o] + FLAGS + ["-D" + d for d in defines]
+                            + (["-DCVX_PART=%d" % part] if part else []))
 
     def run(cmd):
         if verbose:

@@ -117,7 +117,9 @@ __host__ __device__ constexpr int igemm_filter_octet_pitch(int KT, int OCT)
     return KT * 16 + (OCT > 1 ? (128 / OCT < 16 ? 16 : 128 / OCT) : 0);
 }
 
-template <int DT, int WM, int WN, int TM, int TN, int CC, int TAPS, int UA, int UB>
+// RAGGED: the group's channels are not a multiple of CC, and the last stage's missing ones are cleared on their way
+// into LDS.  A kernel of its own: in one kernel the clearing, though it never ran, cost the 56x56 layer 12.3 -> 13.4 us.
+template <int DT, int WM, int WN, int TM, int TN, int CC, int TAPS, int UA, int UB, bool RAGGED>
 __global__ void __launch_bounds__((WM * WN + igemm_producer_waves(TM, TN, TAPS, UA, UB)) * 64)
 igemm_kernel(ConvArgs a, IgemmGeom g)
 {
@@ -254,19 +256,15 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
 #pragma unroll
             for (int u = 0; u < UA; ++u) {
                 if (a_oct[u] >= 0) {
-                    const int c0 = cbase + a_oct[u] * 8;
+                    // channels past the group's end re-read the unit's first channel (store_stage clears them)
+                    const int live = RAGGED ? g.cg - (cbase + a_oct[u] * 8) : 8;
                     const long long off0 = a_goff[u] + (long long)cbase * HW;
-                    const bool fast = off0 >= 0 && off0 + 7LL * HW + 8 <= x_total && c0 + 8 <= g.cg;
-                    if (fast) {
+                    if (live >= 8 && off0 >= 0 && off0 + 7LL * HW + 8 <= x_total) {
 #pragma unroll
                         for (int j = 0; j < 8; ++j) ra[u][j] = *(const u32x4_a2*)(xg + off0 + (long long)j * HW);
-                    } else {
+                    } else if (live > 0) {
 #pragma unroll
-                        for (int j = 0; j < 8; ++j) {
-                            u32x4 v = {0u, 0u, 0u, 0u};
-                            if (c0 + j < g.cg) v = load8(xg, off0 + (long long)j * HW, x_total);
-                            ra[u][j] = v;
-                        }
+                        for (int j = 0; j < 8; ++j) ra[u][j] = load8(xg, off0 + (j < live ? (long long)j * HW : 0LL), x_total);
                     }
                 }
             }
@@ -274,32 +272,45 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
 #pragma unroll
                 for (int u = 0; u < UB; ++u) {
                     if (b_oct[u] >= 0) {
-                        const int k = k0 + b_k[u];
-                        const int c0 = cbase + b_oct[u] * 8;
+                        // filters past the group's end re-read its last one (their outputs are never stored);
+                        // channels past the end are the next filter's first (store_stage clears them)
+                        const int k = min(k0 + b_k[u], k_end - 1);
+                        const int c0 = RAGGED ? min(cbase + b_oct[u] * 8, (g.cg - 1) & ~7) : cbase + b_oct[u] * 8;
                         const long long off0 = ((long long)k * g.cg + c0) * TAPS;
-                        const bool full = k < k_end && c0 + 8 <= g.cg;
-                        if (full) {
+                        if (!RAGGED || off0 + 8 * BROWS <= w_total) {
 #pragma unroll
-                            for (int i = 0; i < BROWS; ++i) {
-                                if (i * 8 + 8 <= 8 * TAPS) rbv[u][i] = *(const u32x4_a2*)(wg + off0 + i * 8);
-                                else rbv[u][i] = load8(wg, off0 + i * 8, w_total);
-                            }
+                            for (int i = 0; i < BROWS; ++i) rbv[u][i] = *(const u32x4_a2*)(wg + off0 + i * 8);
                         } else {
-                            // ragged: filters past K or channels past C contribute zeros
 #pragma unroll
-                            for (int i = 0; i < BROWS; ++i) {
-                                u32x4 v = {0u, 0u, 0u, 0u};
-#pragma unroll
-                                for (int e = 0; e < 8; ++e) {
-                                    const int t = i * 8 + e;          // = j * TAPS + tap
-                                    const int j = t / TAPS;
-                                    if (k < k_end && j < 8 && c0 + j < g.cg)
-                                        v[e >> 1] |= ((uint32_t)wg[off0 + t]) << ((e & 1) * 16);
-                                }
-                                rbv[u][i] = v;
-                            }
+                            for (int i = 0; i < BROWS; ++i) rbv[u][i] = load8(wg, off0 + i * 8, w_total);
                         }
                     }
+                }
+            }
+        };
+        // The last stage's channels past the end of the group contribute zeros.
+        auto clear_tail = [&](u32x4 (&ra)[UA][8], u32x4 (&rbv)[UB][BROWS]) __attribute__((always_inline)) {
+            const int cbase = (g.n_stages - 1) * CC;
+#pragma unroll
+            for (int u = 0; u < UA; ++u) {
+                const int live = g.cg - (cbase + a_oct[u] * 8);
+#pragma unroll
+                for (int j = 0; j < 8; ++j)
+#pragma unroll
+                    for (int d = 0; d < 4; ++d) ra[u][j][d] = j < live ? ra[u][j][d] : 0u;
+            }
+            if constexpr (TAPS > 0) {
+#pragma unroll
+                for (int u = 0; u < UB; ++u) {
+                    const int live = (g.cg - (cbase + b_oct[u] * 8)) * TAPS;          // elements that count
+#pragma unroll
+                    for (int i = 0; i < BROWS; ++i)
+#pragma unroll
+                        for (int d = 0; d < 4; ++d) {
+                            const int e = i * 8 + 2 * d;
+                            const uint32_t keep = (e < live ? 0x0000ffffu : 0u) | (e + 1 < live ? 0xffff0000u : 0u);
+                            rbv[u][i][d] &= keep;
+                        }
                 }
             }
         };
@@ -348,9 +359,12 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
             }
         };
 
-        auto store_stage = [&](int st, int buf, const StageRegs& R) {
+        auto store_stage = [&](int st, int buf, StageRegs& R) {
             auto& ra = R.ra;
             auto& rbv = R.rbv;
+            if constexpr (RAGGED) {
+                if (st == g.n_stages - 1) clear_tail(ra, rbv);
+            }
             unsigned char* xs = smem + BUF0 + buf * stage_bytes;
             unsigned char* ws = xs + g.xbytes;
 #pragma unroll
@@ -411,8 +425,8 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
         // thread (no registers for two sets of them), and not for the twelve-wave kernels: their eight
         // producer waves already keep the memory pipeline full, and two stages of loads in flight per
         // wave measured slower (c5a 45.2 us against 43.9).
-        constexpr bool FASTABLE = TAPS > 0 && UA == 1 && UB == 1 && !SPLIT;
-        bool fast_lane = FASTABLE && (g.n_stages & 1) == 0 && g.cg % CC == 0 && k0 + KT <= k_end;
+        constexpr bool FASTABLE = TAPS > 0 && UA == 1 && UB == 1 && !SPLIT && !RAGGED;
+        bool fast_lane = FASTABLE && (g.n_stages & 1) == 0;
         long long w_goff[UB];
         int w_dst[UB];
         {
@@ -427,7 +441,7 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
                 const int ub = utid + u * UTHREADS;
                 const bool live = ub < g.b_units;
                 const int k = live ? ub / OCT : 0, oct = live ? ub % OCT : 0;
-                w_goff[u] = ((long long)(k0 + k) * g.cg + oct * 8) * (TAPS > 0 ? TAPS : 1);
+                w_goff[u] = ((long long)min(k0 + k, k_end - 1) * g.cg + oct * 8) * (TAPS > 0 ? TAPS : 1);
                 w_dst[u] = live ? oct * WOP + k * 16 : -1;
             }
         }
@@ -990,6 +1004,54 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
     CVX_TRACE_MARK(15);
 }
 
+// The kernels, dealt over the objects this file is compiled into (each takes the compiler about ten seconds).
+// name: igemm_<pixels per block>x<filters per block>_c<channels per stage>_<taps>; waves and 32-wide tiles along
+// pixels and filters, channels per stage, taps, loader units per thread
+#define IGEMM_PART_1(X)                                   \
+    X("igemm_512x64_c32_3x3", 4, 1, 4, 2, 32, 9, 1, 1)     \
+    X("igemm_512x64_c16_3x3", 4, 1, 4, 2, 16, 9, 1, 1)
+#define IGEMM_PART_2(X)                                   \
+    X("igemm_256x128_c16_3x3", 4, 1, 2, 4, 16, 9, 1, 1)    \
+    X("igemm_256x64_c32_3x3", 4, 1, 2, 2, 32, 9, 1, 1)
+#define IGEMM_PART_3(X)                                   \
+    X("igemm_256x64_c16_3x3", 4, 1, 2, 2, 16, 9, 1, 1)     \
+    X("igemm_256x64_c16_3x3_u2", 4, 1, 2, 2, 16, 9, 2, 1)
+#define IGEMM_PART_4(X)                                   \
+    X("igemm_128x128_c32_3x3", 2, 2, 2, 2, 32, 9, 1, 2)    \
+    X("igemm_512x64_c32_1x1", 4, 1, 4, 2, 32, 1, 1, 1)
+#define IGEMM_PART_5(X)                                   \
+    X("igemm_512x64_c64_1x1", 4, 1, 4, 2, 64, 1, 2, 2)     \
+    X("igemm_256x64_c32_1x1", 4, 1, 2, 2, 32, 1, 1, 1)
+#define IGEMM_PART_6(X)                                   \
+    X("igemm_256x64_c64_1x1", 4, 1, 2, 2, 64, 1, 1, 2)     \
+    X("igemm_128x128_c64_1x1", 2, 2, 2, 2, 64, 1, 1, 4)    \
+    X("igemm_256x64_c16_any", 4, 1, 2, 2, 16, 0, 2, 1)
+#define IGEMM_INSTANTIATE(nm, WM, WN, TM, TN, CC, TAPS, UA, UB)                                      \
+    template __global__ void igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, false>(ConvArgs, IgemmGeom); \
+    template __global__ void igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, true>(ConvArgs, IgemmGeom);  \
+    template __global__ void igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, false>(ConvArgs, IgemmGeom);  \
+    template __global__ void igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, true>(ConvArgs, IgemmGeom);
+#if CVX_PART == 1
+IGEMM_PART_1(IGEMM_INSTANTIATE)
+#elif CVX_PART == 2
+IGEMM_PART_2(IGEMM_INSTANTIATE)
+#elif CVX_PART == 3
+IGEMM_PART_3(IGEMM_INSTANTIATE)
+#elif CVX_PART == 4
+IGEMM_PART_4(IGEMM_INSTANTIATE)
+#elif CVX_PART == 5
+IGEMM_PART_5(IGEMM_INSTANTIATE)
+#elif CVX_PART == 6
+IGEMM_PART_6(IGEMM_INSTANTIATE)
+#else
+#define IGEMM_ELSEWHERE(nm, WM, WN, TM, TN, CC, TAPS, UA, UB)                                               \
+    extern template __global__ void igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, false>(ConvArgs, IgemmGeom); \
+    extern template __global__ void igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, true>(ConvArgs, IgemmGeom);  \
+    extern template __global__ void igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, false>(ConvArgs, IgemmGeom);  \
+    extern template __global__ void igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, true>(ConvArgs, IgemmGeom);
+#define IGEMM_ALL(X) IGEMM_PART_1(X) IGEMM_PART_2(X) IGEMM_PART_3(X) IGEMM_PART_4(X) IGEMM_PART_5(X) IGEMM_PART_6(X)
+IGEMM_ALL(IGEMM_ELSEWHERE)
+
 // ------------------------------------------------------------------------------------------------
 // host side: tile geometry, variant table, launch
 // ------------------------------------------------------------------------------------------------
@@ -1000,30 +1062,17 @@ constexpr int LDS_LIMIT = 160 * 1024;
 struct Variant {
     const char* name;
     int WM, WN, TM, TN, CC, TAPS, UA, UB;     // waves / tiles along pixels (M) and filters (N)
-    void (*kern_bf16)(ConvArgs, IgemmGeom);
-    void (*kern_f16)(ConvArgs, IgemmGeom);
+    void (*kern[2][2])(ConvArgs, IgemmGeom);   // [fp16][ragged channels]
 };
 
 #define IGEMM_VARIANT(nm, WM, WN, TM, TN, CC, TAPS, UA, UB)                                          \
-    {nm, WM, WN, TM, TN, CC, TAPS, UA, UB, igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB>, \
-     igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB>}
+    {nm, WM, WN, TM, TN, CC, TAPS, UA, UB,                                                           \
+     {{igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, false>,                               \
+       igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, true>},                               \
+      {igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, false>,                                \
+       igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, true>}}},
 
-// name: igemm_<pixels per block>x<filters per block>_c<channels per stage>_<taps>
-const Variant kVariants[] = {
-    IGEMM_VARIANT("igemm_512x64_c32_3x3", 4, 1, 4, 2, 32, 9, 1, 1),
-    IGEMM_VARIANT("igemm_512x64_c16_3x3", 4, 1, 4, 2, 16, 9, 1, 1),
-    IGEMM_VARIANT("igemm_256x128_c16_3x3", 4, 1, 2, 4, 16, 9, 1, 1),
-    IGEMM_VARIANT("igemm_256x64_c32_3x3", 4, 1, 2, 2, 32, 9, 1, 1),
-    IGEMM_VARIANT("igemm_256x64_c16_3x3", 4, 1, 2, 2, 16, 9, 1, 1),
-    IGEMM_VARIANT("igemm_256x64_c16_3x3_u2", 4, 1, 2, 2, 16, 9, 2, 1),
-    IGEMM_VARIANT("igemm_128x128_c32_3x3", 2, 2, 2, 2, 32, 9, 1, 2),
-    IGEMM_VARIANT("igemm_512x64_c32_1x1", 4, 1, 4, 2, 32, 1, 1, 1),
-    IGEMM_VARIANT("igemm_512x64_c64_1x1", 4, 1, 4, 2, 64, 1, 2, 2),
-    IGEMM_VARIANT("igemm_256x64_c32_1x1", 4, 1, 2, 2, 32, 1, 1, 1),
-    IGEMM_VARIANT("igemm_256x64_c64_1x1", 4, 1, 2, 2, 64, 1, 1, 2),
-    IGEMM_VARIANT("igemm_128x128_c64_1x1", 2, 2, 2, 2, 64, 1, 1, 4),
-    IGEMM_VARIANT("igemm_256x64_c16_any", 4, 1, 2, 2, 16, 0, 2, 1),
-};
+const Variant kVariants[] = {IGEMM_ALL(IGEMM_VARIANT)};
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
 FastDiv fast_div(int d)
@@ -1245,7 +1294,7 @@ hipError_t igemm_prepare()
 {
     static const hipError_t status = [] {
         for (int i = 0; i < kNumVariants; ++i) {
-            for (auto kern : {kVariants[i].kern_bf16, kVariants[i].kern_f16}) {
+            for (auto kern : {kVariants[i].kern[0][0], kVariants[i].kern[0][1], kVariants[i].kern[1][0], kVariants[i].kern[1][1]}) {
                 hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS_LIMIT);
                 if (e != hipSuccess) return e;
             }
@@ -1262,9 +1311,11 @@ hipError_t igemm_launch(const ConvArgs& a, const LaunchPlan& p, hipStream_t s)
     const Variant& v = kVariants[p.variant];
     IgemmGeom g;
     memcpy(&g, p.geom, sizeof g);
-    auto kern = a.dtype == DT_BF16 ? v.kern_bf16 : v.kern_f16;
+    auto kern = v.kern[a.dtype == DT_F16][g.cg % v.CC != 0];
     hipLaunchKernelGGL(kern, dim3(p.grid_x), dim3(p.block), p.lds, s, a, g);
     return hipGetLastError();
 }
+
+#endif  // CVX_PART
 
 }  // namespace cvx
