@@ -1017,7 +1017,6 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
     X("igemm_256x64_c16_3x3", 4, 1, 2, 2, 16, 9, 1, 1)     \
     X("igemm_256x64_c16_3x3_u2", 4, 1, 2, 2, 16, 9, 2, 1)
 #define IGEMM_PART_4(X)                                   \
-    X("igemm_128x128_c32_3x3", 2, 2, 2, 2, 32, 9, 1, 2)    \
     X("igemm_512x64_c32_1x1", 4, 1, 4, 2, 32, 1, 1, 1)
 #define IGEMM_PART_5(X)                                   \
     X("igemm_512x64_c64_1x1", 4, 1, 4, 2, 64, 1, 2, 2)     \
