@@ -102,10 +102,11 @@ __device__ __forceinline__ int lds_slot(int s) { return s + (s >> 3); }
 // producers' vector-ALU and memory work runs in the shadow of the matrix pipe.  One s_barrier per
 // stage hands a finished buffer from producers to consumers and a drained one back.
 // 8: four producer waves for the input and four for the filters; 4: four that do both (kernels whose
-// registers do not allow three waves per SIMD: 4x2 register tiles, or several 3x3 loader units per thread).
+// registers do not allow three waves per SIMD: 4x2 register tiles, several 3x3 loader units per thread, or the 100
+// registers of a 5x5 filter unit).
 __host__ __device__ constexpr int igemm_producer_waves(int TM, int TN, int TAPS, int UA, int UB)
 {
-    return (TM * TN <= 4 && !(TAPS == 9 && (UA > 1 || UB > 1))) ? 8 : 4;
+    return (TM * TN <= 4 && !(TAPS == 9 && (UA > 1 || UB > 1)) && TAPS != 25) ? 8 : 4;
 }
 
 // Filter region of a stage: [tap][octet][filter] x 16 bytes.  The loader's lanes are dealt octet-fastest, so
@@ -425,7 +426,7 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
         // thread (no registers for two sets of them), and not for the twelve-wave kernels: their eight
         // producer waves already keep the memory pipeline full, and two stages of loads in flight per
         // wave measured slower (c5a 45.2 us against 43.9).
-        constexpr bool FASTABLE = TAPS > 0 && UA == 1 && UB == 1 && !SPLIT && !RAGGED;
+        constexpr bool FASTABLE = TAPS > 0 && UA == 1 && UB == 1 && !SPLIT && !RAGGED && TAPS < 25;
         bool fast_lane = FASTABLE && (g.n_stages & 1) == 0;
         long long w_goff[UB];
         int w_dst[UB];
@@ -588,7 +589,7 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
         // column s of filter row 0 (octet `half`); further filter rows are a constant row_bytes away.
         // Kernels built for a fixed filter size keep one offset per filter column; the others keep the
         // logical element index and derive the address per tap.
-        constexpr int NSW = TAPS == 9 ? 3 : 1;
+        constexpr int NSW = TAPS == 9 ? 3 : TAPS == 25 ? 5 : TAPS == 7 ? 7 : 1;   // 1x7 and 7x1: one per tap
         const int oct_bytes = g.NB * g.PSLOTS * 16;
         const int row_bytes = a.dil_h * g.WP * 18;                 // one filter row down, in bytes
         int xb[TM][NSW];
@@ -613,7 +614,10 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
             xl[tm] = valid ? py * a.stride_h * g.WP + px * a.stride_w : zero_col;
             xr[tm] = (valid ? img * g.PSLOTS * 16 : 0) + half * oct_bytes;
 #pragma unroll
-            for (int sw = 0; sw < NSW; ++sw) xb[tm][sw] = xr[tm] + lds_slot(xl[tm] + sw * a.dil_w) * 16;
+            for (int sw = 0; sw < NSW; ++sw) {
+                const bool down = TAPS == 7 && a.S == 1;
+                xb[tm][sw] = xr[tm] + lds_slot(xl[tm] + (down ? 0 : sw * a.dil_w)) * 16 + (down ? sw * row_bytes : 0);
+            }
         }
         const int b_lane = ((wn * TN) * 32 + l32) * 16 + half * WOP;
         const bool wave_on = wm < n_ptiles;            // this wave owns at least one live pixel tile
@@ -661,7 +665,7 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
             if (!wave_on) return;
             const unsigned char* xs = smem + BUF0 + buf * stage_bytes;
             const unsigned char* ws = xs + g.xbytes + b_lane;
-            if constexpr (TAPS == 9 || TAPS == 1) {
+            if constexpr (TAPS > 0) {
                 constexpr int NS = TAPS * KSTEPS;
                 const int xs_off = lds0 + BUF0 + buf * stage_bytes;
                 // Fragments are read PF k-steps ahead of their MFMAs.  A step of 2x2 tiles is only
@@ -675,10 +679,10 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
                 int pa[TM];                                       // addresses of the pixel fragments of one k-step
                 auto pixel_addresses = [&](int step) {
                     const int tap = step / KSTEPS, kk = step % KSTEPS;
-                    const int soff = xs_off + (TAPS == 9 ? tap / 3 : 0) * row_bytes + 2 * kk * oct_bytes;   // wave-uniform
+                    const int soff = xs_off + (TAPS == 9 || TAPS == 25 ? tap / NSW : 0) * row_bytes + 2 * kk * oct_bytes;   // wave-uniform
 #pragma unroll
                     for (int tm = 0; tm < TM; ++tm) {
-                        pa[tm] = xb[tm][TAPS == 9 ? tap % 3 : 0] + soff;
+                        pa[tm] = xb[tm][tap % NSW] + soff;
                         asm volatile("" : "+v"(pa[tm]));           // computed here, not where it is used
                     }
                 };
@@ -1025,6 +1029,11 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
     X("igemm_256x64_c64_1x1", 4, 1, 2, 2, 64, 1, 1, 2)     \
     X("igemm_128x128_c64_1x1", 2, 2, 2, 2, 64, 1, 1, 4)    \
     X("igemm_256x64_c16_any", 4, 1, 2, 2, 16, 0, 2, 1)
+#define IGEMM_PART_7(X)                                   \
+    X("igemm_256x64_c16_5x5", 4, 1, 2, 2, 16, 25, 1, 1)
+#define IGEMM_PART_8(X)                                   \
+    X("igemm_256x64_c16_7", 4, 1, 2, 2, 16, 7, 1, 1)       \
+    X("igemm_256x64_c32_7", 4, 1, 2, 2, 32, 7, 1, 1)
 #define IGEMM_INSTANTIATE(nm, WM, WN, TM, TN, CC, TAPS, UA, UB)                                      \
     template __global__ void igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, false>(ConvArgs, IgemmGeom); \
     template __global__ void igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, true>(ConvArgs, IgemmGeom);  \
@@ -1042,13 +1051,17 @@ IGEMM_PART_4(IGEMM_INSTANTIATE)
 IGEMM_PART_5(IGEMM_INSTANTIATE)
 #elif CVX_PART == 6
 IGEMM_PART_6(IGEMM_INSTANTIATE)
+#elif CVX_PART == 7
+IGEMM_PART_7(IGEMM_INSTANTIATE)
+#elif CVX_PART == 8
+IGEMM_PART_8(IGEMM_INSTANTIATE)
 #else
 #define IGEMM_ELSEWHERE(nm, WM, WN, TM, TN, CC, TAPS, UA, UB)                                               \
     extern template __global__ void igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, false>(ConvArgs, IgemmGeom); \
     extern template __global__ void igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, true>(ConvArgs, IgemmGeom);  \
     extern template __global__ void igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, false>(ConvArgs, IgemmGeom);  \
     extern template __global__ void igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, true>(ConvArgs, IgemmGeom);
-#define IGEMM_ALL(X) IGEMM_PART_1(X) IGEMM_PART_2(X) IGEMM_PART_3(X) IGEMM_PART_4(X) IGEMM_PART_5(X) IGEMM_PART_6(X)
+#define IGEMM_ALL(X) IGEMM_PART_1(X) IGEMM_PART_2(X) IGEMM_PART_3(X) IGEMM_PART_4(X) IGEMM_PART_5(X) IGEMM_PART_7(X) IGEMM_PART_8(X) IGEMM_PART_6(X)
 IGEMM_ALL(IGEMM_ELSEWHERE)
 
 // ------------------------------------------------------------------------------------------------
@@ -1096,7 +1109,8 @@ bool plan(const ConvArgs& a, const Variant& v, int NB, int TH, IgemmGeom* out)
 {
     const int taps = a.R * a.S;
     if (v.TAPS > 0 && v.TAPS != taps) return false;
-    if (v.TAPS == 9 && (a.R != 3 || a.S != 3)) return false;      // the 9-tap kernels index taps as 3 x 3
+    if (v.TAPS == 9 && (a.R != 3 || a.S != 3)) return false;      // the 9-tap kernels index taps as 3 x 3,
+    if (v.TAPS == 25 && (a.R != 5 || a.S != 5)) return false;     // the 25-tap one as 5 x 5
     const int threads = 4 * 64;                    // producer threads
     const int KT = v.WN * v.TN * 32, PT = v.WM * v.TM * 32, OCT = v.CC / 8;
     if (NB < 1 || TH < 1 || NB > a.N || TH > a.Ho) return false;
@@ -1189,8 +1203,11 @@ double cost(const ConvArgs& a, const Variant& v, const IgemmGeom& g, int cus)
     // fixed launch/drain cost, a barrier hand-over per stage, and the fill of the first stage (which
     // nothing overlaps): smaller stages start the matrix pipe sooner
     const double overhead = 3000.0 + 400.0 * g.n_stages + (g.xbytes + g.wbytes) / 16.0;
+    // Filter sizes without a compiled transpose: their filters are gathered and scattered one element at a time, and their
+    // multiply loop waits for every fragment (16x48x35x35 K=72 5x5 fp16: 37.9 us, against 18.5 us with one)
+    const double gather = v.TAPS > 0 ? 0.0 : (double)g.n_stages * (v.WN * v.TN * 32 * v.CC) / 256 * (a.R * a.S) * 30.0;
     const double staged = (double)blocks * g.n_stages * (g.xbytes + g.wbytes) / cus / 64.0;   // 64 B/clk/CU
-    return (double)rounds * (mfma + overhead) + staged;
+    return (double)rounds * (mfma + overhead + gather) + staged;
 }
 
 const Variant* find_variant(const char* name, size_t len)

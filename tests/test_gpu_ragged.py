@@ -33,3 +33,35 @@ def test_ragged_channels_and_filters(w, dtype):
                                      "igemm_256x64_c16_3x3"])
 def test_every_3x3_variant(variant):
     check_case(_c(name="pinned", N=3, C=43, K=150, H=12, W=12), pin=variant + ",1,10")
+
+
+def _f(R, S, **kw):
+    return _c(name="%dx%d" % (R, S), R=R, S=S, **kw)
+
+
+TALL_AND_WIDE = [
+    _f(5, 5, N=2, C=16, K=64, H=9, W=40, pad=(2, 2)),
+    _f(5, 5, N=3, C=43, K=72, H=35, W=35, pad=(2, 2)),
+    _f(5, 5, N=5, C=32, K=33, H=7, W=7, pad=(0, 0)),
+    _f(5, 5, N=2, C=48, K=65, H=23, W=21, pad=(4, 4), dil=(2, 2)),
+    _f(5, 5, N=2, C=24, K=30, H=20, W=18, pad=(2, 1), stride=(2, 2)),
+    _f(5, 5, N=2, C=51, K=42, H=13, W=13, pad=(2, 2), groups=3),
+    _f(1, 7, N=2, C=32, K=64, H=17, W=17, pad=(0, 3)),
+    _f(1, 7, N=3, C=21, K=70, H=12, W=40, pad=(0, 3)),
+    _f(7, 1, N=2, C=64, K=64, H=40, W=12, pad=(3, 0)),
+    _f(7, 1, N=3, C=37, K=31, H=15, W=15, pad=(3, 0)),
+    _f(7, 1, N=4, C=16, K=48, H=8, W=8, pad=(0, 0)),
+    _f(1, 7, N=2, C=48, K=50, H=14, W=30, pad=(1, 6), dil=(1, 2), stride=(2, 1)),
+    _f(7, 1, N=2, C=48, K=50, H=30, W=14, pad=(6, 1), dil=(2, 1), stride=(1, 2)),
+]
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F16])
+@pytest.mark.parametrize("w", TALL_AND_WIDE, ids=lambda w: "%s_c%d_h%d" % (w.name, w.C, w.H))
+def test_compiled_filter_sizes(w, dtype):
+    assert check_case(wl.small_variant(w, dtype=dtype)).rsplit("_", 1)[1] in ("5x5", "7")
+
+
+@pytest.mark.parametrize("variant", ["igemm_256x64_c16_7", "igemm_256x64_c32_7"])
+def test_both_seven_tap_kernels(variant):
+    check_case(_f(7, 1, N=3, C=43, K=150, H=12, W=12, pad=(3, 0)), pin=variant + ",1,10")
