@@ -20,7 +20,7 @@ SOURCES = ["cvx_api.cpp", "kernels_direct.hip", "kernels_igemm.hip", "kernels_st
            "kernels_tiled_f32.hip", "kernels_grouped.hip"]
 # Sources whose kernels are dealt over further objects (the same file with -DCVX_PART=1..n), so that a build uses the
 # machine's cores: one kernel of the implicit-GEMM family takes the compiler about ten seconds.
-PARTS = {"kernels_igemm.hip": 8}
+PARTS = {"kernels_igemm.hip": 9}
 HEADERS = ["cvx_internal.h", "cvx_device.h", os.path.join("..", "..", "include", "cvx.h")]
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",

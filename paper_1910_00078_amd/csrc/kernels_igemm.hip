@@ -58,6 +58,7 @@ struct IgemmGeom {
     int xbytes, wbytes;   // LDS bytes per stage for input and filters
     int flat;        // output staging: 0 = [filter][pixel] tile; 1, 2 = the tile's run of y, image by image (see the epilogue)
     int flat_pitch;  // elements per image of that staging
+    int part_off;    // LDS offset of the partial sums (kernels whose waves split the reduction)
     FastDiv by_wo, by_w, by_upi, by_nb, by_kblocks, by_rowblocks, by_howo, by_kpx;
 };
 
@@ -120,11 +121,16 @@ __host__ __device__ constexpr int igemm_filter_octet_pitch(int KT, int OCT)
 
 // RAGGED: the group's channels are not a multiple of CC, and the last stage's missing ones are cleared on their way
 // into LDS.  A kernel of its own: in one kernel the clearing, though it never ran, cost the 56x56 layer 12.3 -> 13.4 us.
-template <int DT, int WM, int WN, int TM, int TN, int CC, int TAPS, int UA, int UB, bool RAGGED>
-__global__ void __launch_bounds__((WM * WN + igemm_producer_waves(TM, TN, TAPS, UA, UB)) * 64)
+// KS: the consumer waves split the channels of a stage KS ways, and the first of them adds the others' sums in LDS before
+// the epilogue.  Small problems (one image, few pixels) leave most of the chip idle and are bound by the chain of
+// stages, each a load latency, a transpose and a hand-over of about 0.8 us however little it multiplies; a small tile
+// with 64 channels a stage has more blocks and a half to a quarter of the stages, and splitting them over waves
+// keeps their multiply time below the producers'.  1x256x14x14 K=256: 256x64 tiles with 32 channels 17.4 us, this 8.6.
+template <int DT, int WM, int WN, int TM, int TN, int CC, int TAPS, int UA, int UB, int KS, bool RAGGED>
+__global__ void __launch_bounds__((WM * WN * KS + igemm_producer_waves(TM, TN, TAPS, UA, UB)) * 64)
 igemm_kernel(ConvArgs a, IgemmGeom g)
 {
-    constexpr int NCW = WM * WN;           // consumer waves
+    constexpr int NCW = WM * WN * KS;      // consumer waves
     // Producer waves.  Kernels with 2x2 register tiles leave room for twelve waves per block (three per
     // SIMD, 168 registers each): four producer waves load the input and four more the filters, which
     // halves each producer's chain of loads, transposes and LDS writes per stage.  The 4x2 kernels
@@ -137,7 +143,8 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
     constexpr int KT = WN * TN * 32;       // filters per block   (MFMA B operand / D columns)
     constexpr int PT = WM * TM * 32;       // pixels per block    (MFMA A operand / D rows)
     constexpr int OCT = CC / 8;
-    constexpr int KSTEPS = CC / 16;
+    constexpr int KSTEPS = CC / 16 / KS;   // k-steps of a wave per stage and tap
+    static_assert(CC % (16 * KS) == 0, "whole k-steps");
     constexpr int PTP = PT + 8;            // pixel pitch of the staged output tile
     constexpr int WOP = igemm_filter_octet_pitch(KT, OCT);   // bytes between the octets of one tap in the filter region
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
@@ -578,12 +585,14 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
                 __syncthreads();                           // stage st consumed, stage st+1 in LDS
             }
         }
+        if constexpr (KS > 1) __syncthreads();             // the consumers' partial sums
     } else {
         // =========================================================================================
         // consumer waves
         // =========================================================================================
         const int l32 = lane & 31, half = lane >> 5;
-        const int wm = wave / WN, wn = wave % WN;
+        const int ks = wave / (WM * WN), wmn = wave % (WM * WN);
+        const int wm = wmn / WN, wn = wmn % WN;
 
         // Per-lane LDS byte offsets for each of the wave's pixel tiles: xb[tm][s] addresses filter
         // column s of filter row 0 (octet `half`); further filter rows are a constant row_bytes away.
@@ -612,14 +621,14 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
             // element 0.
             const int zero_col = (g.WP - a.W >= (a.S - 1) * a.dil_w + 1) ? a.W + a.pad_w : 0;
             xl[tm] = valid ? py * a.stride_h * g.WP + px * a.stride_w : zero_col;
-            xr[tm] = (valid ? img * g.PSLOTS * 16 : 0) + half * oct_bytes;
+            xr[tm] = (valid ? img * g.PSLOTS * 16 : 0) + (half + 2 * ks * KSTEPS) * oct_bytes;
 #pragma unroll
             for (int sw = 0; sw < NSW; ++sw) {
                 const bool down = TAPS == 7 && a.S == 1;
                 xb[tm][sw] = xr[tm] + lds_slot(xl[tm] + (down ? 0 : sw * a.dil_w)) * 16 + (down ? sw * row_bytes : 0);
             }
         }
-        const int b_lane = ((wn * TN) * 32 + l32) * 16 + half * WOP;
+        const int b_lane = ((wn * TN) * 32 + l32) * 16 + (half + 2 * ks * KSTEPS) * WOP;
         const bool wave_on = wm < n_ptiles;            // this wave owns at least one live pixel tile
 
         // epilogue constants of this lane's filters: only the loads are issued here; they are turned
@@ -792,7 +801,7 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
         for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
             for (int tn = 0; tn < TN; ++tn) {
-                const float seed = has_bn ? 0.0f : ca[tn].add;
+                const float seed = has_bn || ks > 0 ? 0.0f : ca[tn].add;
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[tm][tn][r] = seed;
             }
@@ -824,6 +833,23 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
         }
 #endif
 
+        if constexpr (KS > 1) {
+            // the stage buffers are drained (the last stage's barrier); this region lies past the output tile
+            float* part = (float*)(smem + g.part_off) + ((ks - 1) * (WM * WN) + wmn) * (TM * TN * 16 * 64) + lane;
+            if (ks > 0 && wave_on) {
+#pragma unroll
+                for (int i = 0; i < TM * TN * 16; ++i) part[i * 64] = acc[i / 16 / TN][i / 16 % TN][i % 16];
+            }
+            __syncthreads();
+            if (ks == 0 && wave_on) {
+#pragma unroll
+                for (int s = 1; s < KS; ++s)
+#pragma unroll
+                    for (int i = 0; i < TM * TN * 16; ++i)
+                        acc[i / 16 / TN][i / 16 % TN][i % 16] += part[(s * (WM * WN) * (TM * TN * 16) + i) * 64];
+            }
+        }
+
         // ---- epilogue, part 1: batch-norm / activation on the accumulators in registers, one
         //      rounding to the output type, then the tile goes into LDS as [filter][pixel].
         // Two stagings.  Ordinarily the tile is [filter][pixel] and the store below walks along the
@@ -834,7 +860,7 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
         // pieces of LDS are aligned 16-byte pieces of y.  The store is then a plain copy.  Where each
         // pixel goes comes from a table the producers wrote in the prologue.
         uint16_t* ot = (uint16_t*)(smem + BUF0);
-        if (wave_on) {
+        if (wave_on && ks == 0) {
             const int* ftab = (const int*)(smem + BUF0 + 2 * stage_bytes);
             // Runs of y: a lane's four consecutive pixels stay together when the planes are multiples of
             // 4 pixels; otherwise every pixel has its own place.
@@ -1012,33 +1038,36 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
 // name: igemm_<pixels per block>x<filters per block>_c<channels per stage>_<taps>; waves and 32-wide tiles along
 // pixels and filters, channels per stage, taps, loader units per thread
 #define IGEMM_PART_1(X)                                   \
-    X("igemm_512x64_c32_3x3", 4, 1, 4, 2, 32, 9, 1, 1)     \
-    X("igemm_512x64_c16_3x3", 4, 1, 4, 2, 16, 9, 1, 1)
+    X("igemm_512x64_c32_3x3", 4, 1, 4, 2, 32, 9, 1, 1, 1)     \
+    X("igemm_512x64_c16_3x3", 4, 1, 4, 2, 16, 9, 1, 1, 1)
 #define IGEMM_PART_2(X)                                   \
-    X("igemm_256x128_c16_3x3", 4, 1, 2, 4, 16, 9, 1, 1)    \
-    X("igemm_256x64_c32_3x3", 4, 1, 2, 2, 32, 9, 1, 1)
+    X("igemm_256x128_c16_3x3", 4, 1, 2, 4, 16, 9, 1, 1, 1)    \
+    X("igemm_256x64_c32_3x3", 4, 1, 2, 2, 32, 9, 1, 1, 1)
 #define IGEMM_PART_3(X)                                   \
-    X("igemm_256x64_c16_3x3", 4, 1, 2, 2, 16, 9, 1, 1)     \
-    X("igemm_256x64_c16_3x3_u2", 4, 1, 2, 2, 16, 9, 2, 1)
+    X("igemm_256x64_c16_3x3", 4, 1, 2, 2, 16, 9, 1, 1, 1)     \
+    X("igemm_256x64_c16_3x3_u2", 4, 1, 2, 2, 16, 9, 2, 1, 1)
 #define IGEMM_PART_4(X)                                   \
-    X("igemm_512x64_c32_1x1", 4, 1, 4, 2, 32, 1, 1, 1)
+    X("igemm_512x64_c32_1x1", 4, 1, 4, 2, 32, 1, 1, 1, 1)
 #define IGEMM_PART_5(X)                                   \
-    X("igemm_512x64_c64_1x1", 4, 1, 4, 2, 64, 1, 2, 2)     \
-    X("igemm_256x64_c32_1x1", 4, 1, 2, 2, 32, 1, 1, 1)
+    X("igemm_512x64_c64_1x1", 4, 1, 4, 2, 64, 1, 2, 2, 1)     \
+    X("igemm_256x64_c32_1x1", 4, 1, 2, 2, 32, 1, 1, 1, 1)
 #define IGEMM_PART_6(X)                                   \
-    X("igemm_256x64_c64_1x1", 4, 1, 2, 2, 64, 1, 1, 2)     \
-    X("igemm_128x128_c64_1x1", 2, 2, 2, 2, 64, 1, 1, 4)    \
-    X("igemm_256x64_c16_any", 4, 1, 2, 2, 16, 0, 2, 1)
+    X("igemm_256x64_c64_1x1", 4, 1, 2, 2, 64, 1, 1, 2, 1)     \
+    X("igemm_128x128_c64_1x1", 2, 2, 2, 2, 64, 1, 1, 4, 1)    \
+    X("igemm_256x64_c16_any", 4, 1, 2, 2, 16, 0, 2, 1, 1)
 #define IGEMM_PART_7(X)                                   \
-    X("igemm_256x64_c16_5x5", 4, 1, 2, 2, 16, 25, 1, 1)
+    X("igemm_256x64_c16_5x5", 4, 1, 2, 2, 16, 25, 1, 1, 1)
+#define IGEMM_PART_9(X)                                   \
+    X("igemm_64x32_c64_3x3", 2, 1, 1, 1, 64, 9, 1, 1, 2)   \
+    X("igemm_64x32_c32_3x3", 2, 1, 1, 1, 32, 9, 1, 1, 2)
 #define IGEMM_PART_8(X)                                   \
-    X("igemm_256x64_c16_7", 4, 1, 2, 2, 16, 7, 1, 1)       \
-    X("igemm_256x64_c32_7", 4, 1, 2, 2, 32, 7, 1, 1)
-#define IGEMM_INSTANTIATE(nm, WM, WN, TM, TN, CC, TAPS, UA, UB)                                      \
-    template __global__ void igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, false>(ConvArgs, IgemmGeom); \
-    template __global__ void igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, true>(ConvArgs, IgemmGeom);  \
-    template __global__ void igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, false>(ConvArgs, IgemmGeom);  \
-    template __global__ void igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, true>(ConvArgs, IgemmGeom);
+    X("igemm_256x64_c16_7", 4, 1, 2, 2, 16, 7, 1, 1, 1)       \
+    X("igemm_256x64_c32_7", 4, 1, 2, 2, 32, 7, 1, 1, 1)
+#define IGEMM_INSTANTIATE(nm, WM, WN, TM, TN, CC, TAPS, UA, UB, KS)                                      \
+    template __global__ void igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, KS, false>(ConvArgs, IgemmGeom); \
+    template __global__ void igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, KS, true>(ConvArgs, IgemmGeom);  \
+    template __global__ void igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, KS, false>(ConvArgs, IgemmGeom);  \
+    template __global__ void igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, KS, true>(ConvArgs, IgemmGeom);
 #if CVX_PART == 1
 IGEMM_PART_1(IGEMM_INSTANTIATE)
 #elif CVX_PART == 2
@@ -1055,13 +1084,15 @@ IGEMM_PART_6(IGEMM_INSTANTIATE)
 IGEMM_PART_7(IGEMM_INSTANTIATE)
 #elif CVX_PART == 8
 IGEMM_PART_8(IGEMM_INSTANTIATE)
+#elif CVX_PART == 9
+IGEMM_PART_9(IGEMM_INSTANTIATE)
 #else
-#define IGEMM_ELSEWHERE(nm, WM, WN, TM, TN, CC, TAPS, UA, UB)                                               \
-    extern template __global__ void igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, false>(ConvArgs, IgemmGeom); \
-    extern template __global__ void igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, true>(ConvArgs, IgemmGeom);  \
-    extern template __global__ void igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, false>(ConvArgs, IgemmGeom);  \
-    extern template __global__ void igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, true>(ConvArgs, IgemmGeom);
-#define IGEMM_ALL(X) IGEMM_PART_1(X) IGEMM_PART_2(X) IGEMM_PART_3(X) IGEMM_PART_4(X) IGEMM_PART_5(X) IGEMM_PART_7(X) IGEMM_PART_8(X) IGEMM_PART_6(X)
+#define IGEMM_ELSEWHERE(nm, WM, WN, TM, TN, CC, TAPS, UA, UB, KS)                                               \
+    extern template __global__ void igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, KS, false>(ConvArgs, IgemmGeom); \
+    extern template __global__ void igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, KS, true>(ConvArgs, IgemmGeom);  \
+    extern template __global__ void igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, KS, false>(ConvArgs, IgemmGeom);  \
+    extern template __global__ void igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, KS, true>(ConvArgs, IgemmGeom);
+#define IGEMM_ALL(X) IGEMM_PART_1(X) IGEMM_PART_2(X) IGEMM_PART_3(X) IGEMM_PART_4(X) IGEMM_PART_5(X) IGEMM_PART_7(X) IGEMM_PART_8(X) IGEMM_PART_9(X) IGEMM_PART_6(X)
 IGEMM_ALL(IGEMM_ELSEWHERE)
 
 // ------------------------------------------------------------------------------------------------
@@ -1073,16 +1104,16 @@ constexpr int LDS_LIMIT = 160 * 1024;
 
 struct Variant {
     const char* name;
-    int WM, WN, TM, TN, CC, TAPS, UA, UB;     // waves / tiles along pixels (M) and filters (N)
+    int WM, WN, TM, TN, CC, TAPS, UA, UB, KS; // waves / tiles along pixels (M) and filters (N)
     void (*kern[2][2])(ConvArgs, IgemmGeom);   // [fp16][ragged channels]
 };
 
-#define IGEMM_VARIANT(nm, WM, WN, TM, TN, CC, TAPS, UA, UB)                                          \
-    {nm, WM, WN, TM, TN, CC, TAPS, UA, UB,                                                           \
-     {{igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, false>,                               \
-       igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, true>},                               \
-      {igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, false>,                                \
-       igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, true>}}},
+#define IGEMM_VARIANT(nm, WM, WN, TM, TN, CC, TAPS, UA, UB, KS)                                          \
+    {nm, WM, WN, TM, TN, CC, TAPS, UA, UB, KS,                                                           \
+     {{igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, KS, false>,                               \
+       igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, KS, true>},                               \
+      {igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, KS, false>,                                \
+       igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, KS, true>}}},
 
 const Variant kVariants[] = {IGEMM_ALL(IGEMM_VARIANT)};
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
@@ -1095,11 +1126,14 @@ FastDiv fast_div(int d)
     return f;
 }
 
+int partial_bytes(const Variant& v) { return (v.KS - 1) * v.WM * v.WN * v.TM * v.TN * 4096; }
+
 int lds_bytes(const Variant& v, const IgemmGeom& g)
 {
     const int KT = v.WN * v.TN * 32, PT = v.WM * v.TM * 32;
     const int stages = 16 + 2 * (g.xbytes + g.wbytes) + (g.flat ? PT * 4 : 0);   // + the table of staging offsets
     const int otile = 16 + (g.flat ? (g.NB + 1) * g.flat_pitch * 2 : KT * (PT + 8) * 2);
+    if (v.KS > 1 && g.part_off + partial_bytes(v) > stages) return g.part_off + partial_bytes(v);
     return stages > otile ? stages : otile;
 }
 
@@ -1155,6 +1189,9 @@ bool plan(const ConvArgs& a, const Variant& v, int NB, int TH, IgemmGeom* out)
             if ((long long)(NB + 1) * g.flat_pitch * 2 > 2 * (xb + wb) || lds_bytes(v, g) > LDS_LIMIT) g.flat = 0;
         }
     }
+    // partial sums after the output tile, and before the table of staging offsets that follows the stage buffers
+    g.part_off = (16 + (g.flat ? (NB + 1) * g.flat_pitch * 2 : KT * (PT + 8) * 2) + 15) & ~15;
+    if (v.KS > 1 && g.flat && g.part_off + partial_bytes(v) > 16 + 2 * (xb + wb)) return false;
     if (lds_bytes(v, g) > LDS_LIMIT) return false;
     if ((long long)g.row_blocks * g.img_blocks * g.k_blocks > 0x7fffffffLL) return false;
     g.by_wo = fast_div(a.Wo);
@@ -1199,10 +1236,12 @@ double cost(const ConvArgs& a, const Variant& v, const IgemmGeom& g, int cus)
     const int used = (g.NB * g.TH * a.Wo + 31) / 32;
     // every wave multiplies all TM of its tiles (dead ones included) unless it has none at all
     const int per_wave = used >= 1 ? v.TM : 0;
-    const double mfma = 32.0 * per_wave * v.TN * (a.R * a.S) * (v.CC / 16) * g.n_stages;
+    const double mfma = 32.0 * per_wave * v.TN * (a.R * a.S) * (v.CC / 16 / v.KS) * g.n_stages;
     // fixed launch/drain cost, a barrier hand-over per stage, and the fill of the first stage (which
     // nothing overlaps): smaller stages start the matrix pipe sooner
-    const double overhead = 3000.0 + 400.0 * g.n_stages + (g.xbytes + g.wbytes) / 16.0;
+    // (400 cycles), which with the producers' work takes 1500 whatever it multiplies
+    const double hand_over = mfma / g.n_stages + 400.0 < 1500.0 ? 1500.0 - mfma / g.n_stages : 400.0;
+    const double overhead = 3000.0 + hand_over * g.n_stages + (g.xbytes + g.wbytes) / 16.0;
     // Filter sizes without a compiled transpose: their filters are gathered and scattered one element at a time, and their
     // multiply loop waits for every fragment (16x48x35x35 K=72 5x5 fp16: 37.9 us, against 18.5 us with one)
     const double gather = v.TAPS > 0 ? 0.0 : (double)g.n_stages * (v.WN * v.TN * 32 * v.CC) / 256 * (a.R * a.S) * 30.0;
@@ -1225,7 +1264,7 @@ void fill_plan(const ConvArgs& a, const Variant& v, const IgemmGeom& g, LaunchPl
     out->variant = (int)(&v - kVariants);
     out->grid_x = (unsigned)(g.row_blocks * g.img_blocks * g.k_blocks);
     out->grid_y = 1;
-    out->block = (unsigned)((v.WM * v.WN + igemm_producer_waves(v.TM, v.TN, v.TAPS, v.UA, v.UB)) * 64);
+    out->block = (unsigned)((v.WM * v.WN * v.KS + igemm_producer_waves(v.TM, v.TN, v.TAPS, v.UA, v.UB)) * 64);
     out->lds = lds_bytes(v, g);
     memcpy(out->geom, &g, sizeof g);
 }

@@ -65,3 +65,14 @@ def test_compiled_filter_sizes(w, dtype):
 @pytest.mark.parametrize("variant", ["igemm_256x64_c16_7", "igemm_256x64_c32_7"])
 def test_both_seven_tap_kernels(variant):
     check_case(_f(7, 1, N=3, C=43, K=150, H=12, W=12, pad=(3, 0)), pin=variant + ",1,10")
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F16])
+@pytest.mark.parametrize("variant", ["igemm_64x32_c64_3x3", "igemm_64x32_c32_3x3"])
+@pytest.mark.parametrize("w,tile", [(_c(name="rows", N=2, C=64, K=32, H=14, W=14), "1,4"), (_c(name="ragged", N=3, C=75, K=33, H=9, W=20), "1,3"),
+                                    (_c(name="images", N=5, C=130, K=40, H=5, W=5), "2,5"), (_c(name="one", N=1, C=8, K=9, H=8, W=8), "1,8"),
+                                    (_c(name="narrow", N=2, C=96, K=64, H=6, W=3), "1,6"),
+                                    (_c(name="s2", N=2, C=70, K=70, H=15, W=13, stride=(2, 2)), "1,8"),
+                                    (_c(name="groups", N=2, C=120, K=66, H=7, W=7, groups=3), "1,7")], ids=lambda v: getattr(v, "name", None))
+def test_split_reduction(variant, w, tile, dtype):
+    check_case(wl.small_variant(w, dtype=dtype), pin=variant + "," + tile)
