@@ -1056,13 +1056,15 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
     X("igemm_128x128_c64_1x1", 2, 2, 2, 2, 64, 1, 1, 4, 1)    \
     X("igemm_256x64_c16_any", 4, 1, 2, 2, 16, 0, 2, 1, 1)
 #define IGEMM_PART_7(X)                                   \
-    X("igemm_256x64_c16_5x5", 4, 1, 2, 2, 16, 25, 1, 1, 1)
+    X("igemm_256x64_c16_5x5", 4, 1, 2, 2, 16, 25, 1, 1, 1)  \
+    X("igemm_64x32_c32_5x5", 2, 1, 1, 1, 32, 25, 1, 1, 2)
 #define IGEMM_PART_9(X)                                   \
     X("igemm_64x32_c64_3x3", 2, 1, 1, 1, 64, 9, 1, 1, 2)   \
     X("igemm_64x32_c32_3x3", 2, 1, 1, 1, 32, 9, 1, 1, 2)
 #define IGEMM_PART_8(X)                                   \
     X("igemm_256x64_c16_7", 4, 1, 2, 2, 16, 7, 1, 1, 1)       \
-    X("igemm_256x64_c32_7", 4, 1, 2, 2, 32, 7, 1, 1, 1)
+    X("igemm_256x64_c32_7", 4, 1, 2, 2, 32, 7, 1, 1, 1)     \
+    X("igemm_64x32_c64_7", 2, 1, 1, 1, 64, 7, 1, 1, 2)
 #define IGEMM_INSTANTIATE(nm, WM, WN, TM, TN, CC, TAPS, UA, UB, KS)                                      \
     template __global__ void igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, KS, false>(ConvArgs, IgemmGeom); \
     template __global__ void igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, KS, true>(ConvArgs, IgemmGeom);  \

@@ -62,9 +62,14 @@ def test_compiled_filter_sizes(w, dtype):
     assert check_case(wl.small_variant(w, dtype=dtype)).rsplit("_", 1)[1] in ("5x5", "7")
 
 
-@pytest.mark.parametrize("variant", ["igemm_256x64_c16_7", "igemm_256x64_c32_7"])
+@pytest.mark.parametrize("variant", ["igemm_256x64_c16_7", "igemm_256x64_c32_7", "igemm_64x32_c64_7"])
 def test_both_seven_tap_kernels(variant):
-    check_case(_f(7, 1, N=3, C=43, K=150, H=12, W=12, pad=(3, 0)), pin=variant + ",1,10")
+    check_case(_f(7, 1, N=3, C=43, K=150, H=12, W=12, pad=(3, 0)), pin=variant + (",1,5" if "64x32" in variant else ",1,10"))
+
+
+@pytest.mark.parametrize("C", [16, 43, 64])
+def test_split_5x5(C):
+    check_case(_f(5, 5, N=3, C=C, K=50, H=12, W=14, pad=(2, 2)), pin="igemm_64x32_c32_5x5,1,4")
 
 
 @pytest.mark.parametrize("dtype", [wl.BF16, wl.F16])
