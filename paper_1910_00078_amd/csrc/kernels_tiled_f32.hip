@@ -19,6 +19,7 @@
 #include "cvx_device.h"
 
 #include <cstring>
+#include <type_traits>
 
 namespace cvx {
 
@@ -34,31 +35,39 @@ struct Geom {
     int xfloats, wfloats;        // LDS floats per buffer for input and filters
     int xorg;                    // LDS rows start with xorg unused floats, so that image column 0 sits on a 16-byte boundary (vector staging)
     int x_units, w_units;        // 16-byte pieces staged per chunk (vector staging)
-    int vec;                     // 1: the vector-staging kernel runs
+    int vec;                     // the vector-staging kernel runs: 1 on aligned pieces, 2 on pieces at any float
 };
 
 
 constexpr int THREADS = 256;
 constexpr int XE = 16;           // input elements a thread stages per chunk, at most
 constexpr int WE = 24;           // filter elements a thread stages per chunk, at most
-constexpr int XV = 4, WV = 6;    // the same in 16-byte pieces (vector staging)
+constexpr int XV = 4;            // input pieces of 16 bytes a thread stages per chunk (vector staging)
+constexpr int filter_pieces(int vec) { return vec == 2 ? 7 : 6; }   // and filter pieces
 
 // WM x WN waves, each TM x TN tiles of 32 pixels x 32 filters; CC channels per chunk; TAPS = R * S
 // compiled in (the multiply loop is then fully unrolled, with the next step's fragments read while the
 // current step multiplies), or 0 for any filter size.
-// VEC: the chunk is staged in 16-byte pieces (image rows and filter rows that are multiples of four floats on
-// 16-byte boundaries, whole channel chunks): a quarter of the load and LDS-write instructions and half the
-// registers of the element-wise staging, which serves every other shape.
-template <int WM, int WN, int TM, int TN, int CC, int TAPS, bool VEC>
+// VEC: the chunk is staged in 16-byte pieces: a quarter of the load and LDS-write instructions and half the registers of
+// the element-wise staging (VEC = 0).  1: image rows and filter rows are multiples of four floats on 16-byte
+// boundaries, whole channel chunks.  2: any row of four floats or more (a row's last piece is moved back to end with
+// it), any channel count; kernels of their own, since the tests they need cost the aligned 56x56 layer 88.5 -> 93.7 us.
+// KS: the waves split a chunk's channels KS ways and add their sums in LDS at the end.  For problems of few tiles, which
+// are bound by the chain of chunks (about 1 us each however little it multiplies):
+// 1x224x25x25 K=32 3x3 128 -> 31 us, 4x179x12x12 K=70 1x1 65 -> 18 us.
+template <int WM, int WN, int TM, int TN, int CC, int TAPS, int VEC, int KS = 1>
 __global__ void __launch_bounds__(THREADS) tiled_f32_kernel(ConvArgs a, Geom g)
 {
-    static_assert(WM * WN * 64 == THREADS && CC % 2 == 0 && CC <= 16 && XE <= 16 && WE <= 32, "four waves, channel pairs, 4-bit channel indices");
+    static_assert(WM * WN * KS * 64 == THREADS && CC % (2 * KS) == 0 && CC <= 16 && XE <= 16 && WE <= 32, "four waves, channel pairs, 4-bit channel indices");
+    constexpr int WV = filter_pieces(VEC);
+    constexpr int CP = CC / 2 / KS;                    // channel pairs of a wave per chunk
     constexpr int KT = WN * TN * 32;
     extern __shared__ __attribute__((aligned(16))) float lds[];
     warm_kernel_arguments<sizeof(ConvArgs) + sizeof(Geom)>();
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave / WN, wn = wave % WN;
+    const int ks = wave / (WM * WN), wmn = wave % (WM * WN);
+    const int wm = wmn / WN, wn = wmn % WN;
     const int taps = TAPS > 0 ? TAPS : a.R * a.S;
     const int HW = a.H * a.W, HoWo = a.Ho * a.Wo;
 
@@ -87,6 +96,8 @@ __global__ void __launch_bounds__(THREADS) tiled_f32_kernel(ConvArgs a, Geom g)
     unsigned long long x_ch = 0ull;                    // 4 bits per element: its channel inside the chunk
     int w_src[NWE], w_dst[NWE];
     unsigned long long w_ch[2] = {0ull, 0ull};
+    int xv_ch = 0;                                     // 4 bits per piece: its channel inside the chunk
+    int wv_left[NWV];                                  // floats from the piece to the end of its filter row
     int xv_src[NXV], xv_dst[NXV], wv_src[NWV], wv_dst[NWV];   // vector staging: -1 = nothing to fetch (LDS keeps its zeros)
     if constexpr (!VEC) {
         const int per_c = g.NB * g.PH * a.W;
@@ -119,7 +130,7 @@ __global__ void __launch_bounds__(THREADS) tiled_f32_kernel(ConvArgs a, Geom g)
             }
         }
     } else {
-        const int w4 = a.W >> 2, per_c = g.NB * g.PH * w4;
+        const int w4 = (a.W + 3) >> 2, per_c = g.NB * g.PH * w4;
 #pragma unroll
         for (int i = 0; i < XV; ++i) {
             const int u = tid + i * THREADS;
@@ -127,22 +138,25 @@ __global__ void __launch_bounds__(THREADS) tiled_f32_kernel(ConvArgs a, Geom g)
             if (u < g.x_units) {
                 const int c = u / per_c, r1 = u - c * per_c;
                 const int img = r1 / (g.PH * w4), r2 = r1 - img * (g.PH * w4);
-                const int row = r2 / w4, col = 4 * (r2 - row * w4);
+                const int row = r2 / w4, col = VEC == 2 ? min(4 * (r2 - row * w4), a.W - 4) : 4 * (r2 - row * w4);
                 const int h = h_lo + row;
                 if (img < nimg && h >= 0 && h < a.H) {
                     xv_src[i] = ((img * a.C + c) * a.H + h) * a.W + col;
+                    xv_ch |= c << (4 * i);
                     xv_dst[i] = c * g.plane + (img * g.PH + row) * g.WP + g.xorg + a.pad_w + col;
                 }
             }
         }
-        const int per_k = (CC * taps) >> 2;
+        const int per_k = (CC * taps + 3) >> 2;
 #pragma unroll
         for (int i = 0; i < WV; ++i) {
             const int u = tid + i * THREADS;
             wv_src[i] = wv_dst[i] = -1;
+            wv_left[i] = 0;
             if (u < g.w_units) {
-                const int k = u / per_k, j = 4 * (u - k * per_k);
+                const int k = u / per_k, j = min(4 * (u - k * per_k), CC * taps - 4);
                 if (k0 + k < k_end) {
+                    wv_left[i] = g.cg * taps - j;
                     wv_src[i] = k * g.cg * taps + j;
                     wv_dst[i] = k * g.wpitch + j;
                 }
@@ -155,6 +169,8 @@ __global__ void __launch_bounds__(THREADS) tiled_f32_kernel(ConvArgs a, Geom g)
     float xr[NXE], wr[NWE];
     typedef float f32x4 __attribute__((ext_vector_type(4)));
     typedef float f32x2v __attribute__((ext_vector_type(2)));
+    typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
+    typedef typename std::conditional<VEC == 2, f32x4_a4, f32x4>::type piece_t;
     f32x4 xr4[NXV], wr4[NWV];
     auto load_chunk = [&](int st) {
         const int c0 = st * CC;
@@ -174,16 +190,25 @@ __global__ void __launch_bounds__(THREADS) tiled_f32_kernel(ConvArgs a, Geom g)
         } else {
             const float* xc = xg + x_base + (size_t)c0 * HW;
             const float* wc = wg + w_base + (size_t)c0 * taps;
+            const bool ragged = c0 + CC > g.cg;                     // the last chunk, channels missing
 #pragma unroll
             for (int i = 0; i < XV; ++i) {
                 f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
-                if (xv_src[i] >= 0) v = *(const f32x4*)(xc + xv_src[i]);
+                if (xv_src[i] >= 0 && (VEC == 1 || !ragged || c0 + ((xv_ch >> (4 * i)) & 15) < g.cg)) v = *(const piece_t*)(xc + xv_src[i]);
                 xr4[i] = v;
             }
 #pragma unroll
             for (int i = 0; i < WV; ++i) {
                 f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
-                if (wv_src[i] >= 0) v = *(const f32x4*)(wc + wv_src[i]);
+                if (wv_src[i] >= 0) {
+                    if (VEC == 1 || !ragged || wv_left[i] >= c0 * taps + 4) {
+                        v = *(const piece_t*)(wc + wv_src[i]);
+                    } else {                                        // the row ends inside or before the piece
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (e < wv_left[i] - c0 * taps) v[e] = wc[wv_src[i] + e];
+                    }
+                }
                 wr4[i] = v;
             }
         }
@@ -201,12 +226,16 @@ __global__ void __launch_bounds__(THREADS) tiled_f32_kernel(ConvArgs a, Geom g)
         } else {
 #pragma unroll
             for (int i = 0; i < XV; ++i)
-                if (xv_dst[i] >= 0) *(f32x4*)(xs + xv_dst[i]) = xr4[i];
+                if (xv_dst[i] >= 0) *(piece_t*)(xs + xv_dst[i]) = xr4[i];
 #pragma unroll
             for (int i = 0; i < WV; ++i)
                 if (wv_dst[i] >= 0) {                              // filter rows are 8-byte, not 16-byte aligned in LDS
-                    *(f32x2v*)(ws + wv_dst[i]) = f32x2v{wr4[i][0], wr4[i][1]};
-                    *(f32x2v*)(ws + wv_dst[i] + 2) = f32x2v{wr4[i][2], wr4[i][3]};
+                    if constexpr (VEC == 2) {
+                        *(f32x4_a4*)(ws + wv_dst[i]) = wr4[i];
+                    } else {
+                        *(f32x2v*)(ws + wv_dst[i]) = f32x2v{wr4[i][0], wr4[i][1]};
+                        *(f32x2v*)(ws + wv_dst[i] + 2) = f32x2v{wr4[i][2], wr4[i][3]};
+                    }
                 }
         }
     };
@@ -223,10 +252,10 @@ __global__ void __launch_bounds__(THREADS) tiled_f32_kernel(ConvArgs a, Geom g)
             rem = f - img * ppi;
         }
         const int py = rem / a.Wo, px = rem - py * a.Wo;
-        xo[tm] = g.xorg + (f < npix ? ((img * g.PH + py * a.stride_h) * g.WP + px * a.stride_w) + half * g.plane : half * g.plane);
+        xo[tm] = g.xorg + (f < npix ? ((img * g.PH + py * a.stride_h) * g.WP + px * a.stride_w) + half * g.plane : half * g.plane) + 2 * ks * CP * g.plane;
     }
 #pragma unroll
-    for (int tn = 0; tn < TN; ++tn) wo[tn] = g.xfloats + ((wn * TN + tn) * 32 + l32) * g.wpitch + half * taps;
+    for (int tn = 0; tn < TN; ++tn) wo[tn] = g.xfloats + ((wn * TN + tn) * 32 + l32) * g.wpitch + (half + 2 * ks * CP) * taps;
 
     f32x16 acc[TM][TN];
 #pragma unroll
@@ -246,7 +275,7 @@ __global__ void __launch_bounds__(THREADS) tiled_f32_kernel(ConvArgs a, Geom g)
         if (st + 1 < g.n_stages) load_chunk(st + 1);
         const float* xs = lds + (st & 1) * buf_floats;
         if constexpr (TAPS > 0) {
-            constexpr int NS = (CC / 2) * TAPS;
+            constexpr int NS = CP * TAPS;
             float fa[2][TM], fb[2][TN];
             auto read_step = [&](int set, int step) {
                 const int cp = step / TAPS, tap = step % TAPS;
@@ -269,7 +298,7 @@ __global__ void __launch_bounds__(THREADS) tiled_f32_kernel(ConvArgs a, Geom g)
                         acc[tm][tn] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[t & 1][tm], fb[t & 1][tn], acc[tm][tn], 0, 0, 0);
             }
         } else {
-            for (int cp = 0; cp < CC / 2; ++cp) {
+            for (int cp = 0; cp < CP; ++cp) {
                 int tap = 0;
                 for (int r = 0; r < a.R; ++r) {
                     for (int s = 0; s < a.S; ++s, ++tap) {
@@ -291,6 +320,22 @@ __global__ void __launch_bounds__(THREADS) tiled_f32_kernel(ConvArgs a, Geom g)
         }
         if (st + 1 < g.n_stages) store_chunk((st + 1) & 1);
         __syncthreads();
+    }
+
+    if constexpr (KS > 1) {
+        // the chunk buffers are drained (the last chunk's barrier)
+        float* part = lds + ((ks - 1) * (WM * WN) + wmn) * (TM * TN * 16 * 64) + lane;
+        if (ks > 0) {
+#pragma unroll
+            for (int i = 0; i < TM * TN * 16; ++i) part[i * 64] = acc[i / 16 / TN][i / 16 % TN][i % 16];
+        }
+        __syncthreads();
+        if (ks > 0) return;
+#pragma unroll
+        for (int s = 1; s < KS; ++s)
+#pragma unroll
+            for (int i = 0; i < TM * TN * 16; ++i)
+                acc[i / 16 / TN][i / 16 % TN][i % 16] += part[(s * (WM * WN) * (TM * TN * 16) + i) * 64];
     }
 
     // ---- epilogue in registers, one store.  A lane holds, per (tm, tn), filter l32 at the 16 pixels
@@ -340,20 +385,31 @@ __global__ void __launch_bounds__(THREADS) tiled_f32_kernel(ConvArgs a, Geom g)
 
 struct Variant {
     const char* name;
-    int WM, WN, TM, TN, CC, TAPS;
-    void (*kern)(ConvArgs, Geom);
-    void (*kern_vec)(ConvArgs, Geom);      // vector staging, or null
+    int WM, WN, TM, TN, CC, TAPS, KS;
+    void (*kern[3])(ConvArgs, Geom);       // by staging, or null
 };
+
+#define F32_VARIANT(nm, WM, WN, TM, TN, CC, TAPS)                                                \
+    {nm, WM, WN, TM, TN, CC, TAPS, 1, {tiled_f32_kernel<WM, WN, TM, TN, CC, TAPS, 0>, tiled_f32_kernel<WM, WN, TM, TN, CC, TAPS, 1>, \
+                                       tiled_f32_kernel<WM, WN, TM, TN, CC, TAPS, 2>}}
+#define F32_SMALL(nm, WM, CC, TAPS, KS) {nm, WM, 1, 1, 1, CC, TAPS, KS, {nullptr, nullptr, tiled_f32_kernel<WM, 1, 1, 1, CC, TAPS, 2, KS>}}
 
 // name: tiled_f32_<pixels per block>x<filters per block>_c<channels per chunk>[_<filter size>]
 const Variant kVariants[] = {
-    {"tiled_f32_256x64_c8_3x3", 4, 1, 2, 2, 8, 9, tiled_f32_kernel<4, 1, 2, 2, 8, 9, false>, tiled_f32_kernel<4, 1, 2, 2, 8, 9, true>},
-    {"tiled_f32_128x64_c8_3x3", 4, 1, 1, 2, 8, 9, tiled_f32_kernel<4, 1, 1, 2, 8, 9, false>, tiled_f32_kernel<4, 1, 1, 2, 8, 9, true>},
-    {"tiled_f32_256x64_c16_1x1", 4, 1, 2, 2, 16, 1, tiled_f32_kernel<4, 1, 2, 2, 16, 1, false>, tiled_f32_kernel<4, 1, 2, 2, 16, 1, true>},
-    {"tiled_f32_256x64_c8", 4, 1, 2, 2, 8, 0, tiled_f32_kernel<4, 1, 2, 2, 8, 0, false>, tiled_f32_kernel<4, 1, 2, 2, 8, 0, true>},
-    {"tiled_f32_128x64_c8", 4, 1, 1, 2, 8, 0, tiled_f32_kernel<4, 1, 1, 2, 8, 0, false>, tiled_f32_kernel<4, 1, 1, 2, 8, 0, true>},
-    {"tiled_f32_128x32_c8", 4, 1, 1, 1, 8, 0, tiled_f32_kernel<4, 1, 1, 1, 8, 0, false>, tiled_f32_kernel<4, 1, 1, 1, 8, 0, true>},
-    {"tiled_f32_128x32_c2", 4, 1, 1, 1, 2, 0, tiled_f32_kernel<4, 1, 1, 1, 2, 0, false>, nullptr},
+    F32_VARIANT("tiled_f32_256x64_c8_3x3", 4, 1, 2, 2, 8, 9),
+    F32_VARIANT("tiled_f32_128x64_c8_3x3", 4, 1, 1, 2, 8, 9),
+    F32_VARIANT("tiled_f32_256x64_c16_1x1", 4, 1, 2, 2, 16, 1),
+    F32_VARIANT("tiled_f32_256x64_c8", 4, 1, 2, 2, 8, 0),
+    F32_VARIANT("tiled_f32_128x64_c8", 4, 1, 1, 2, 8, 0),
+    F32_VARIANT("tiled_f32_128x32_c8", 4, 1, 1, 1, 8, 0),
+    F32_SMALL("tiled_f32_128x32_c4", 4, 4, 0, 1),
+    F32_SMALL("tiled_f32_64x32_c16_3x3", 2, 16, 9, 2),
+    F32_SMALL("tiled_f32_64x32_c16", 2, 16, 0, 2),
+    F32_SMALL("tiled_f32_64x32_c8", 2, 8, 0, 2),
+    F32_SMALL("tiled_f32_32x32_c16_3x3", 1, 16, 9, 4),
+    F32_SMALL("tiled_f32_32x32_c16", 1, 16, 0, 4),
+    F32_SMALL("tiled_f32_32x32_c8", 1, 8, 0, 4),
+    {"tiled_f32_128x32_c2", 4, 1, 1, 1, 2, 0, 1, {tiled_f32_kernel<4, 1, 1, 1, 2, 0, 0>, nullptr, nullptr}},
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 constexpr int LDS_LIMIT = 64 * 1024;        // two blocks per compute unit and room to spare
@@ -362,6 +418,7 @@ bool plan(const ConvArgs& a, const Variant& v, int NB, int TH, bool aligned16, G
 {
     const int taps = a.R * a.S;
     const int KT = v.WN * v.TN * 32, PT = v.WM * v.TM * 32;
+    const int w4 = (a.W + 3) / 4, p4 = (v.CC * taps + 3) / 4;      // 16-byte pieces of an image row, of a filter's chunk
     if (v.TAPS > 0 && (v.TAPS != taps || (v.TAPS == 9 && a.R != 3))) return false;
     if (NB < 1 || TH < 1 || NB > a.N || TH > a.Ho) return false;
     if (NB > 1 && TH != a.Ho) return false;
@@ -376,15 +433,21 @@ bool plan(const ConvArgs& a, const Variant& v, int NB, int TH, bool aligned16, G
     const int need = (a.Wo - 1) * a.stride_w + (a.S - 1) * a.dil_w + 1;
     g.WP = a.W + 2 * a.pad_w > need ? a.W + 2 * a.pad_w : need;
     g.cg = a.C / a.groups;
-    // vector staging: 16-byte pieces of image rows and of a filter's chunk row must start on 16-byte
-    // boundaries in device memory and (image rows) in LDS, and chunks must be whole
-    g.vec = v.kern_vec != nullptr && aligned16 && a.W % 4 == 0 && g.cg % v.CC == 0 && (v.CC * taps) % 4 == 0 &&
-            (long long)v.CC * NB * g.PH * (a.W / 4) <= (long long)XV * THREADS && (long long)KT * v.CC * taps / 4 <= (long long)WV * THREADS;
+    // vector staging: 16-byte pieces of image rows and of a filter's chunk row.  Where they start on 16-byte boundaries in
+    // device memory and (image rows) in LDS, and chunks are whole, they stay aligned; else a row's last piece is moved
+    // back to end with the row, pieces are loaded from and written to any float, and the last chunk's missing channels
+    // are cleared.  Element by element the same layers take 1.5 to 3 times as long (13x176x18x18 K=80 3x3: 103 us, 72 in pieces on the same tile).
+    const auto fits = [&](int vec) {
+        return v.kern[vec] && (long long)v.CC * NB * g.PH * w4 <= (long long)XV * THREADS && (long long)KT * p4 <= (long long)filter_pieces(vec) * THREADS;
+    };
+    const bool whole = aligned16 && a.W % 4 == 0 && g.cg % v.CC == 0 && (v.CC * taps) % 4 == 0;
+    g.vec = whole && fits(1) ? 1 : a.W >= 4 && v.CC * taps >= 4 && fits(2) ? 2 : 0;
+    if (!v.kern[g.vec]) return false;
     if (g.vec) {
         g.xorg = (4 - a.pad_w % 4) % 4;                // image column 0 at float xorg + pad_w of a row: a multiple of 4
         g.WP = (g.xorg + g.WP + 3) & ~3;
-        g.x_units = v.CC * NB * g.PH * (a.W / 4);
-        g.w_units = KT * v.CC * taps / 4;
+        g.x_units = v.CC * NB * g.PH * w4;
+        g.w_units = KT * p4;
     }
     // a fragment read takes channel c from lanes 0-31 and channel c+1 from lanes 32-63: 32 floats from the
     // middle of one plane and 32 from the next, which share no LDS bank if planes are 32 (mod 64) floats apart
@@ -397,7 +460,7 @@ bool plan(const ConvArgs& a, const Variant& v, int NB, int TH, bool aligned16, G
     g.img_blocks = (a.N + NB - 1) / NB;
     g.n_stages = (g.cg + v.CC - 1) / v.CC;
     const long long x_elems = (long long)v.CC * NB * g.PH * a.W, w_elems = (long long)KT * v.CC * taps;
-    if (x_elems > (long long)XE * THREADS || w_elems > (long long)WE * THREADS) return false;
+    if (!g.vec && (x_elems > (long long)XE * THREADS || w_elems > (long long)WE * THREADS)) return false;
     // filter fragments: lane l of each half reads row l at the same column, the halves `taps` columns
     // apart.  A pitch of 2 (mod 4) puts the 32 rows on the 32 even banks; an odd `taps` then puts the
     // other half on the odd ones.
@@ -441,16 +504,20 @@ bool tiled_f32_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out)
             tf32::Geom g;
             if (!tf32::plan(a, v, multi ? t : 1, multi ? a.Ho : t, env.aligned16, &g)) continue;
             ++tried;
-            // Estimated cycles: blocks run two to a compute unit and share its matrix pipe; a block's chunk
-            // costs its MFMAs (64 cycles each per wave) over a measured efficiency (on the 56x56 3x3 layer the
-            // 128x64 tile runs at 1.0, 256x64 at 0.8, the loop without a compiled filter size 13 % slower)
-            // plus a fixed hand-over per chunk.
+            // Estimated cycles: blocks run two to a compute unit and share its matrix pipe; a block's chunk costs its
+            // MFMAs (64 cycles each per wave) over a measured efficiency (on the 56x56 3x3 layer the 128x64 tile runs at
+            // 1.0, 256x64 at 0.8 without aligned vector staging, which runs short of registers; the loop without a
+            // compiled filter size 13 % slower) plus a fixed hand-over, and two blocks never take less than the
+            // latency of a chunk's loads.
             const long long blocks = (long long)g.row_blocks * g.img_blocks * g.k_blocks;
-            const long long rounds = (blocks + 2LL * env.cus - 1) / (2LL * env.cus);
-            // (with vector staging the 256x64 tile no longer runs short of registers: 90 against 95 us)
-            const double eff = (v.TM * v.TN == 4 ? (g.vec ? 1.0 : 0.8) : v.TM * v.TN == 2 ? 1.0 : 0.7) * (v.TAPS > 0 ? 1.0 : 0.87);
-            const double chunk = (v.CC / 2) * (double)(a.R * a.S) * v.TM * v.TN * 64.0 / eff + 600.0;
-            const double c = (double)rounds * 2.0 * g.n_stages * chunk;
+            const double per_cu = (double)((blocks + env.cus - 1) / env.cus), pairs = (double)((blocks + 2LL * env.cus - 1) / (2LL * env.cus));
+            const double eff = (v.TM * v.TN == 4 ? (g.vec == 1 ? 1.0 : 0.8) : v.TM * v.TN == 2 ? 1.0 : 0.7) * (v.TAPS > 0 ? 1.0 : 0.87);
+            const double chunk = (v.CC / 2 / v.KS) * (double)(a.R * a.S) * v.TM * v.TN * 64.0 / eff + 600.0;
+            // (a block alone on its unit has nothing to cover its hand-over: 5x80x52x52 K=128, 130 blocks of 256x64 64 us,
+            // 260 of 128x64 58.5); the stores of a tile, 64 cycles an instruction, are four times as many where planes
+            // are not multiples of 16 bytes (4x17x41x41 K=112 1x1: 30 us in 256x64 tiles, 17 in 128x32)
+            const double work = per_cu * chunk + (per_cu < 2.0 ? 1000.0 : 0.0), wait = pairs * 2400.0;
+            const double c = (work > wait ? work : wait) * g.n_stages + per_cu * v.WM * v.WN * v.TM * v.TN * 4 * 64.0 * (HoWo % 4 ? 4 : 1);
             if (c < best) {
                 best = c;
                 bv = &v;
@@ -466,6 +533,8 @@ bool tiled_f32_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out)
     out->grid_y = 1;
     out->block = tf32::THREADS;
     out->lds = 2 * (bg.xfloats + bg.wfloats) * 4;
+    const int partial = (bv->KS - 1) * bv->WM * bv->WN * bv->TM * bv->TN * 4096;
+    if (out->lds < partial) out->lds = partial;
     memcpy(out->geom, &bg, sizeof bg);
     return true;
 }
@@ -474,7 +543,7 @@ hipError_t tiled_f32_prepare()
 {
     static const hipError_t status = [] {
         for (int i = 0; i < tf32::kNumVariants; ++i) {
-            for (auto kern : {tf32::kVariants[i].kern, tf32::kVariants[i].kern_vec}) {
+            for (auto kern : tf32::kVariants[i].kern) {
                 if (!kern) continue;
                 hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, tf32::LDS_LIMIT);
                 if (e != hipSuccess) return e;
@@ -491,7 +560,7 @@ hipError_t tiled_f32_launch(const ConvArgs& a, const LaunchPlan& p, hipStream_t 
     if (e != hipSuccess) return e;
     tf32::Geom g;
     memcpy(&g, p.geom, sizeof g);
-    hipLaunchKernelGGL(g.vec ? tf32::kVariants[p.variant].kern_vec : tf32::kVariants[p.variant].kern, dim3(p.grid_x), dim3(p.block), p.lds, s, a, g);
+    hipLaunchKernelGGL(tf32::kVariants[p.variant].kern[g.vec], dim3(p.grid_x), dim3(p.block), p.lds, s, a, g);
     return hipGetLastError();
 }
 
