@@ -442,27 +442,28 @@ pointwise_kernel(ConvArgs a, Geom g)
 constexpr int LDS_LIMIT = 160 * 1024;
 
 struct Variant {
-    const char* name;
+    const char* name;                          // on whole images of aligned chunks
+    const char* line_name;                     // on other lines: an implicit GEMM over chunks of them
     int WM, WN, TM, TN, CC, NS;
     bool ws;                                   // filters streamed
     void (*kern[2][2])(ConvArgs, Geom);        // [fp16][column stride 2]
 };
 
 #define PW_VARIANT(nm, WM, WN, TM, TN, CC, NS, WS)                                              \
-    {nm, WM, WN, TM, TN, CC, NS, WS,                                                            \
+    {"pointwise_" nm, "igemm_lines_" nm, WM, WN, TM, TN, CC, NS, WS,                                                            \
      {{pointwise_kernel<DT_BF16, WM, WN, TM, TN, CC, NS, 1, WS>, pointwise_kernel<DT_BF16, WM, WN, TM, TN, CC, NS, 2, WS>}, \
       {pointwise_kernel<DT_F16, WM, WN, TM, TN, CC, NS, 1, WS>, pointwise_kernel<DT_F16, WM, WN, TM, TN, CC, NS, 2, WS>}}}
 
-// name: pointwise_<pixels per tile>x<filters per block>_c<channels per stage>_r<ring slots>[_w: filters streamed]
+// name: pointwise_ or igemm_lines_<pixels per tile>x<filters per block>_c<channels per stage>_r<ring slots>[_w: filters streamed]
 const Variant kVariants[] = {
-    PW_VARIANT("pointwise_256x64_c32_r5", 4, 1, 2, 2, 32, 5, false),
-    PW_VARIANT("pointwise_256x64_c32_r3", 4, 1, 2, 2, 32, 3, false),
-    PW_VARIANT("pointwise_128x128_c32_r6", 2, 2, 2, 2, 32, 6, false),
-    PW_VARIANT("pointwise_128x256_c32_r6", 1, 4, 4, 2, 32, 6, false),
-    PW_VARIANT("pointwise_128x64_c32_r6", 2, 1, 2, 2, 32, 6, false),
-    PW_VARIANT("pointwise_128x32_c32_r6", 2, 1, 2, 1, 32, 6, false),
-    PW_VARIANT("pointwise_128x128_c32_r6_w", 2, 2, 2, 2, 32, 6, true),
-    PW_VARIANT("pointwise_256x64_c32_r6_w", 4, 1, 2, 2, 32, 6, true),
+    PW_VARIANT("256x64_c32_r5", 4, 1, 2, 2, 32, 5, false),
+    PW_VARIANT("256x64_c32_r3", 4, 1, 2, 2, 32, 3, false),
+    PW_VARIANT("128x128_c32_r6", 2, 2, 2, 2, 32, 6, false),
+    PW_VARIANT("128x256_c32_r6", 1, 4, 4, 2, 32, 6, false),
+    PW_VARIANT("128x64_c32_r6", 2, 1, 2, 2, 32, 6, false),
+    PW_VARIANT("128x32_c32_r6", 2, 1, 2, 1, 32, 6, false),
+    PW_VARIANT("128x128_c32_r6_w", 2, 2, 2, 2, 32, 6, true),
+    PW_VARIANT("256x64_c32_r6_w", 4, 1, 2, 2, 32, 6, true),
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 
@@ -551,7 +552,7 @@ bool choose(const ConvArgs& a, const PlanEnv& env, Plan* out)
         Plan p;
         if (!plan_variant(a, kVariants[i], env.cus, &p)) continue;
         if (env.pin) {                                               // developer pin: variant name
-            if (strcmp(env.pin, kVariants[i].name) == 0) {
+            if (strcmp(env.pin, kVariants[i].name) == 0 || strcmp(env.pin, kVariants[i].line_name) == 0) {
                 *out = p;
                 return true;
             }
@@ -584,7 +585,7 @@ bool pointwise_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out)
     pw::Plan p;
     if (!pw::choose(a, env, &p)) return false;
     out->id = KID_POINTWISE;
-    out->name = p.v->name;
+    out->name = a.stride_h == 1 && a.stride_w == 1 && p.g.y_aligned ? p.v->name : p.v->line_name;
     out->variant = (int)(p.v - pw::kVariants);
     out->grid_x = (unsigned)p.blocks;
     out->grid_y = 1;
