@@ -591,7 +591,7 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
         // consumer waves
         // =========================================================================================
         const int l32 = lane & 31, half = lane >> 5;
-        const int ks = wave / (WM * WN), wmn = wave % (WM * WN);
+        const int ks = KS > 1 ? wave / (WM * WN) : 0, wmn = KS > 1 ? wave % (WM * WN) : wave;
         const int wm = wmn / WN, wn = wmn % WN;
 
         // Per-lane LDS byte offsets for each of the wave's pixel tiles: xb[tm][s] addresses filter

@@ -66,7 +66,7 @@ __global__ void __launch_bounds__(THREADS) tiled_f32_kernel(ConvArgs a, Geom g)
     warm_kernel_arguments<sizeof(ConvArgs) + sizeof(Geom)>();
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int ks = wave / (WM * WN), wmn = wave % (WM * WN);
+    const int ks = KS > 1 ? wave / (WM * WN) : 0, wmn = KS > 1 ? wave % (WM * WN) : wave;
     const int wm = wmn / WN, wn = wmn % WN;
     const int taps = TAPS > 0 ? TAPS : a.R * a.S;
     const int HW = a.H * a.W, HoWo = a.Ho * a.Wo;
