@@ -407,7 +407,7 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
                     }
                 }
             } else {
-                // any filter size: element-wise gather from global memory, scatter into LDS
+                // other filter sizes: element-wise gather from global memory, scatter into LDS
                 const int cbase = st * CC;
                 for (int pi = filter_wave ? utid : KT * CC; pi < KT * CC; pi += UTHREADS) {
                     const int cl = pi % CC, kl = pi / CC;
