@@ -97,7 +97,7 @@ hipError_t direct_launch(const ConvArgs& a, const LaunchPlan& p, hipStream_t s)
 // piece, else 1); the elements past the last whole piece are done one by one.  In the bias kernel a piece may
 // straddle two channels (planes that are not a multiple of it), never three: planes smaller than a piece go one by
 // one.  The channel of a piece comes from two multiply-high divisions; with 64-bit divisions, one piece a thread and
-// straddling planes element by element, the bias took 13.0 us on 32x512x28x28 bf16; this takes about 8.5.
+// straddling planes element by element, the bias took 13.0 us on 32x512x28x28 bf16 and ReLU 8.2; these take 9.4 and 6.8.
 constexpr int kEwUnroll = 4;
 
 template <int DT, typename F>      // f(value, element of the piece)
