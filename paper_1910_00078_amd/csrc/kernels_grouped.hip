@@ -40,6 +40,28 @@ __device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c)
     else return __builtin_amdgcn_fdot2(__builtin_bit_cast(f16x2, a), __builtin_bit_cast(f16x2, b), c, false);
 }
 
+// One output's sum over the taps inside the image, one product after another.
+template <int DT, int RS, int ST>
+__device__ __forceinline__ float plain_sum(const ConvArgs& a, int cg, int n, int c0, int k, int p, int q)
+{
+    float acc = 0.0f;
+#pragma unroll 1
+    for (int c = 0; c < cg; ++c)
+#pragma unroll 1
+        for (int r = 0; r < RS; ++r) {
+            const int h = p * ST - a.pad_h + r;
+            if (h < 0 || h >= a.H) continue;
+#pragma unroll 1
+            for (int s = 0; s < RS; ++s) {
+                const int v = q * ST - a.pad_w + s;
+                if (v < 0 || v >= a.W) continue;
+                acc = fmaf(Elem<DT>::load(a.x, (((size_t)n * a.C + c0 + c) * a.H + h) * a.W + v),
+                           Elem<DT>::load(a.w, (((size_t)k * cg + c) * RS + r) * RS + s), acc);
+            }
+        }
+    return acc;
+}
+
 // KF filters x TR rows x PX columns per thread; RS x RS filter; stride ST.
 template <int DT, int RS, int ST, int KF, int TR>
 __global__ void __launch_bounds__(256) grouped_kernel(ConvArgs a, Geom g)
@@ -166,8 +188,7 @@ __global__ void __launch_bounds__(256) grouped_kernel(ConvArgs a, Geom g)
         } else {
             // Two taps per instruction (v_dot2_f32_{bf16,f16}: both products and the fp32 accumulator), on the packed
             // pairs as they were loaded and on the same pairs shifted by one element.  The odd last tap of a filter
-            // row shares its pair with the tap before it, whose weight is zero there: every element a pair touches
-            // belongs to the output's own window.
+            // row shares its pair with the tap before it, whose weight is zero there.
             constexpr int NP = RS / 2 + 1;                           // pairs per filter row
             uint32_t wp[KF][RS][NP];
             auto w_at = [&](int f, int j) { return j == NW - 1 ? (uint32_t)r.w_last[f] : (r.w[f][j / 2] >> (16 * (j & 1))) & 0xffffu; };
@@ -228,6 +249,7 @@ __global__ void __launch_bounds__(256) grouped_kernel(ConvArgs a, Geom g)
 
     const bool has_bn = a.bn_scale != nullptr;
     elem_t* __restrict__ yg = (elem_t*)a.y;
+    float any = 0.0f;                                    // a NaN if one of the sums is
     auto write_out = [&](auto&& act_fn) __attribute__((always_inline)) {
 #pragma unroll
         for (int f = 0; f < KF; ++f) {
@@ -238,6 +260,8 @@ __global__ void __launch_bounds__(256) grouped_kernel(ConvArgs a, Geom g)
                 if (p0 + tr >= a.Ho) break;
                 elem_t* dst = yg + (((size_t)n * a.K + k0 + f) * a.Ho + p0 + tr) * a.Wo + q0;
                 float v[PX];
+#pragma unroll
+                for (int q = 0; q < PX; ++q) any += acc[f][tr][q];
 #pragma unroll
                 for (int q = 0; q < PX; ++q) v[q] = act_fn(has_bn ? fmaf(acc[f][tr][q], aff.mul, aff.add) : acc[f][tr][q] + aff.add);
                 uint32_t o[4];
@@ -264,6 +288,23 @@ __global__ void __launch_bounds__(256) grouped_kernel(ConvArgs a, Geom g)
     else if (a.act == ACT_IDENTITY) write_out([](float v) { return v; });
     else if (a.act == ACT_LEAKY_RELU) write_out([&](float v) { return v > 0.0f ? v : a.alpha * v; });
     else write_out([&](float v) { return activate(v, a.act, a.alpha); });
+
+    // The loops above multiply zeros that are no part of the convolution: columns and rows outside the image, and the
+    // other tap of an odd tap's pair.  Against an infinite weight or input such a product is a NaN.  So outputs whose
+    // sums hold a NaN (an infinity or a NaN is among the operands; nothing else makes one) are written again, summed one
+    // tap at a time; finding them costs one addition for each output.
+    if (any != any) {
+#pragma unroll 1
+        for (int f = 0; f < nk; ++f) {
+            const ChannelAffine aff = channel_affine<DT>(a, k0 + f);
+#pragma unroll 1
+            for (int p = p0; p < min(p0 + TR, a.Ho); ++p)
+#pragma unroll 1
+                for (int q = q0; q < min(q0 + PX, a.Wo); ++q)
+                    Elem<DT>::store(yg, (((size_t)n * a.K + k0 + f) * a.Ho + p) * a.Wo + q,
+                                    finish(plain_sum<DT, RS, ST>(a, g.cg, n, grp * g.cg, k0 + f, p, q), aff, has_bn, a.act, a.alpha));
+        }
+    }
 }
 
 struct Variant {

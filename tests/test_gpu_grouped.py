@@ -6,6 +6,7 @@ import pytest
 
 import workloads as wl
 from paper_1910_00078_amd import cvx
+from parity import run_gpu, run_oracle
 from test_gpu_parity import check_case
 
 pytestmark = pytest.mark.gpu
@@ -57,3 +58,34 @@ def test_epilogues_and_unaligned_buffers():
     check_case(w, bias_f32=True)
     for off in [(1, 0, 0), (0, 1, 0), (0, 0, 1)]:
         assert check_case(w, offsets=off).startswith("direct_grouped_")
+
+
+INF = {wl.BF16: 0x7f80, wl.F16: np.float16(np.inf), wl.F32: np.float32(np.inf)}
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F16, wl.F32])
+@pytest.mark.parametrize("where", ["input", "weight", "both"])
+@pytest.mark.parametrize("w", [_g(name="3x3", N=2, C=8, K=8, H=12, W=20, groups=8), _g(name="3x3_s2", N=2, C=8, K=16, H=11, W=19, groups=4, stride=(2, 2)),
+                               _g(name="5x5", N=2, C=6, K=6, H=13, W=17, R=5, S=5, pad=(2, 2), groups=6),
+                               _g(name="four_filters", N=1, C=8, K=24, H=9, W=10, groups=2)], ids=lambda w: w.name)
+def test_an_infinity_reaches_exactly_the_outputs_it_is_part_of(w, where, dtype):
+    """Padding and the zeros that fill up a pair of taps are no part of the sum: an infinite input gives infinities of the
+    weight's sign, an infinite weight leaves the border outputs finite whose tap lies outside the image."""
+    w = wl.small_variant(w, dtype=dtype)
+    x, wt, b = wl.make_inputs(w)
+    x, wt = x.copy(), wt.copy()
+    if where in ("input", "both"):
+        x[0, 1, 4, 7] = x[-1, -1, -1, -1] = x[0, 0, 0, 0] = INF[dtype]
+    if where in ("weight", "both"):
+        wt[1, 0, 0, 0] = wt[-1, -1, -1, -1] = INF[dtype]
+    got, name = run_gpu(w, x, wt, b, act=cvx.CVX_ACT_IDENTITY)
+    assert "grouped_" in name
+    with np.errstate(invalid="ignore"):
+        want = run_oracle(w, x, wt, b, act=cvx.CVX_ACT_IDENTITY)
+    for test in (np.isnan, np.isposinf, np.isneginf):
+        np.testing.assert_array_equal(test(got), test(want))
+    ok = np.isfinite(want)
+    assert 0 < ok.sum() < ok.size
+    # one rounding to the output type of sums of up to 100 products of order one
+    rms = np.sqrt(np.mean(want[ok] ** 2))
+    assert np.all(np.abs(got[ok] - want[ok]) <= {wl.F32: 1e-5, wl.F16: 2e-3, wl.BF16: 1e-2}[dtype] * (np.abs(want[ok]) + 0.1 * rms))
