@@ -20,6 +20,12 @@ CASES = [
     _c(name="c65_k129_s2", N=2, C=65, K=129, H=21, W=23, stride=(2, 2)),
     _c(name="c41_groups3", N=2, C=123, K=45, H=13, W=13, groups=3),
     _c(name="c11_5x5", N=2, C=11, K=20, H=12, W=12, R=5, S=5, pad=(2, 2)),
+    # pieces that reach over both ends of the tensor: planes smaller than a piece, the last image's and filter's tails
+    _c(name="c9_2x2", N=1, C=9, K=9, H=2, W=2),
+    _c(name="c8_1x1", N=1, C=8, K=8, H=1, W=1),
+    _c(name="c17_3x5_pad3", N=2, C=17, K=33, H=3, W=5, pad=(3, 3)),
+    _c(name="c9_groups4", N=2, C=36, K=52, H=12, W=12, groups=4),
+    _c(name="c15_5x5_3x3", N=1, C=15, K=7, H=3, W=3, R=5, S=5, pad=(2, 2)),
 ]
 
 
