@@ -512,12 +512,19 @@ bool tiled_f32_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out)
             const long long blocks = (long long)g.row_blocks * g.img_blocks * g.k_blocks;
             const double per_cu = (double)((blocks + env.cus - 1) / env.cus), pairs = (double)((blocks + 2LL * env.cus - 1) / (2LL * env.cus));
             const double eff = (v.TM * v.TN == 4 ? (g.vec == 1 ? 1.0 : 0.8) : v.TM * v.TN == 2 ? 1.0 : 0.7) * (v.TAPS > 0 ? 1.0 : 0.87);
-            const double chunk = (v.CC / 2 / v.KS) * (double)(a.R * a.S) * v.TM * v.TN * 64.0 / eff + 600.0;
+            // element-wise staging: loads a thread issues per chunk (18x15x73x73 K=129 3x3 stride 2: 128x32_c8 71.4 us that
+            // way, 128x32_c4 in pieces 36.7)
+            const int elements = g.vec ? 0 : (g.x_elems + tf32::THREADS - 1) / tf32::THREADS + (g.w_elems + tf32::THREADS - 1) / tf32::THREADS;
+            const double chunk = (v.CC / 2 / v.KS) * (double)(a.R * a.S) * v.TM * v.TN * 64.0 / eff + 600.0 + 120.0 * elements;
             // (a block alone on its unit has nothing to cover its hand-over: 5x80x52x52 K=128, 130 blocks of 256x64 64 us,
             // 260 of 128x64 58.5); the stores of a tile, 64 cycles an instruction, are four times as many where planes
             // are not multiples of 16 bytes (4x17x41x41 K=112 1x1: 30 us in 256x64 tiles, 17 in 128x32)
-            const double work = per_cu * chunk + (per_cu < 2.0 ? 1000.0 : 0.0), wait = pairs * 2400.0;
-            const double c = (work > wait ? work : wait) * g.n_stages + per_cu * v.WM * v.WN * v.TM * v.TN * 4 * 64.0 * (HoWo % 4 ? 4 : 1);
+            const double work = per_cu * chunk + (per_cu < 2.0 ? 1000.0 : 0.0), wait = pairs * (g.vec ? 2400.0 : 4000.0);
+            // A small tile whose only chunk holds all channels of a filter larger than 1x1 has no loop to hide its prologue, load and exchange of sums in, and
+            // it comes as often as it is small (44x14x31x31 K=96 3x3: 4092 blocks of 32x32 80.5 us, 128x64 tiles 45.2;
+            // 37x16x40x40 K=5 3x3: 1480 of 64x32 27.0, 128x32 16.8; 13x5x25x25 K=112 5x5: 35.7 and 17.0)
+            const double follow = v.KS > 1 && g.n_stages == 1 && a.R * a.S > 1 ? (per_cu - 1.0) * 4500.0 : 0.0;
+            const double c = follow + (work > wait ? work : wait) * g.n_stages + per_cu * v.WM * v.WN * v.TM * v.TN * 4 * 64.0 * (HoWo % 4 ? 4 : 1);
             if (c < best) {
                 best = c;
                 bv = &v;
