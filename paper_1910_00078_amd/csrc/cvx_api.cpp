@@ -218,7 +218,18 @@ bool make_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out)
             if (strncmp(env.pin, "direct", 6) == 0) return direct_plan(a, env, out);
             return false;
         }
-        if (a.groups > 1 && grouped_plan(a, env, out)) return true;
+        if (a.groups > 1 && grouped_plan(a, env, out)) {
+            // In fp32 the matrix pipe gains on the grouped kernel with the filters per group, which that one reads the input
+            // again for (4 at a time in 3x3, each in 5x5): 24x336x9x9 K=2688, 42 groups, 5x5 stride 2 30.3 us tiled and 63.5
+            // grouped, 27x320x6x6 K=20480, 40 groups, 3x3 79 and 119; with 16 filters and fewer the grouped kernel is 1.2-35x
+            // faster, and on rows of fewer than 4 floats, which the tiled kernel stages one by one, mostly too.  The constants
+            // relate the tiled kernel's estimate to its time over 440 layers that both can run.
+            LaunchPlan tiled;
+            if (a.dtype == DT_F32 && (a.W >= 4 || (a.R == 3 && a.stride_h == 1)) && a.C / a.groups >= 4 && a.K / a.groups >= 16 &&
+                tiled_f32_plan(a, env, &tiled) && 6.1 + 1.33 * tiled.us < 0.9 * out->us)
+                *out = tiled;
+            return true;
+        }
         if (pointwise_plan(a, env, out)) return true;
         if (stem_plan(a, env, out)) return true;
         if (igemm_plan(a, env, out)) return true;

@@ -60,6 +60,12 @@ enum KernelId : int {
     KID_COUNT
 };
 
+// The direct kernel splits the channels of a problem of at most this many outputs over neighbouring lanes.
+constexpr long long kDirectSplitOutputs = 32768;
+
+// The tiled fp32 kernel takes problems of at least this many multiply-adds.
+constexpr long long kTiledF32Work = 1LL << 22;
+
 // What a kernel choice may depend on besides the problem itself.  Nothing here is a data pointer: a
 // plan made once serves every later call with the same problem and environment.
 struct PlanEnv {
@@ -76,6 +82,7 @@ struct LaunchPlan {
     int variant;              // index into the family's variant table
     unsigned grid_x, grid_y, block;
     int lds;                  // dynamic LDS bytes
+    double us;                // estimated time of a launch among others, for a choice between families
     alignas(8) unsigned char geom[288];   // the family's geometry struct (a kernel argument)
 };
 

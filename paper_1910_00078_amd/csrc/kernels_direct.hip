@@ -59,7 +59,7 @@ __global__ void __launch_bounds__(256) direct_conv_kernel(ConvArgs a)
 bool direct_plan(const ConvArgs& a, const PlanEnv&, LaunchPlan* out)
 {
     const long long total = (long long)a.N * a.K * a.Ho * a.Wo;
-    const bool split = total <= 32768 && a.C / a.groups >= 8;      // latency-bound sizes
+    const bool split = total <= kDirectSplitOutputs && a.C / a.groups >= 8;      // latency-bound sizes
     long long blocks = (total * (split ? 8 : 1) + 255) / 256;
     if (blocks > (1 << 20)) blocks = 1 << 20;           // grid-stride loop covers the rest
     out->id = KID_DIRECT;

@@ -1,9 +1,9 @@
 // Forward convolution with few input channels per group -- depthwise and grouped layers (Sec. IV-A of the
-// MIOpen paper), and ungrouped layers of a handful of channels -- for square 3x3 and 5x5 filters at stride 1 or 2.
+// MIOpen paper): up to 7 in the 16-bit types, 8 in fp32, square 3x3 and 5x5 filters at stride 1 or 2.
 //
-// With so short a reduction there is nothing for the matrix pipe: the operands would be mostly padding.  What
-// bounds these layers is device memory (depthwise 3x3: 4.5 FLOP per byte) and, at 8 and 16 channels per group,
-// the fp32 vector pipe.  So a thread owns a register tile -- KF filters of one group x TR output rows x PX
+// With so short a reduction there is nothing for the 16-bit matrix pipe: the operands would be mostly padding.  What
+// bounds these layers is device memory (depthwise 3x3: 4.5 FLOP per byte) and, in fp32 with several channels, the
+// vector pipe.  So a thread owns a register tile -- KF filters of one group x TR output rows x PX
 // output columns (PX elements = 16 bytes of y) -- and reads the input rows it needs straight from memory, PX +
 // halo columns at a time; an input element is loaded once per (RS + (TR-1)*ST) / (TR*ST) rows by the thread and
 // the rest of its uses are register reads.  No LDS, no barriers: consecutive lanes read consecutive pieces of
@@ -360,6 +360,20 @@ bool grouped_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out)
     if (a.R != a.S || a.dil_h != 1 || a.dil_w != 1 || a.stride_h != a.stride_w) return false;
     if ((long long)a.H * a.W >= (1LL << 30)) return false;                  // row offsets inside a plane stay in int
     if ((long long)a.N * a.C * a.H * a.W < 32) return false;                // a row piece fits the tensor
+    // Outputs a few pixels wide fill a corner of the 16-byte pieces, and most of their filters' taps lie in the padding, which
+    // this kernel reads and multiplies like the rest and the direct kernel skips.  16-bit, direct against this: width 1
+    // 5.3 and 28.0 us (14x168x1x1 K=10752 5x5, 3 channels), and 16 to 8 on the middle one of 135 drawn layers; width 2 and 3
+    // slower with the fewest channels (1.0-1.4x), faster above; from width 4 on faster (1.4-3x).  fp32 pieces are half as wide: 260 drawn layers of width 1 take 0.2-1.0 of the time
+    // on the direct kernel where the image is one pixel wide, or the filter 5x5, and 1.0-1.3 of it for 3x3 on two pixels.
+    const long long work = (long long)a.N * a.K * a.Ho * a.Wo * cg * a.R * a.S;
+    const bool direct_instead = a.dtype != DT_F32 || work < kTiledF32Work;    // else the tiled fp32 kernel
+    const bool unit3 = a.stride_h == 1 && a.R == 3;
+    const int few = a.dtype == DT_F32 || a.Wo >= 4 ? 1 : a.Wo == 3 ? (a.stride_h == 1 || a.R == 5 ? 1 : 3) : unit3 ? 2 : 4;
+    const bool one = a.Wo == 1 && !(a.dtype == DT_F32 && a.W > 1 && (a.R == 3 || !direct_instead));
+    if (!env.pin && (one || cg < few)) return false;
+    // The direct kernel deals the channels of small problems over lanes from 8 on (4x40x17x17, 5 groups, stride 2: 4.4 us
+    // there, 6.2 here).
+    if (!env.pin && cg >= 8 && direct_instead && (long long)a.N * a.K * a.Ho * a.Wo <= kDirectSplitOutputs) return false;
     // 16-bit types with 8 or more channels per group go to the matrix pipe (8 channels: 6.3 against 15.7 us on
     // 15x96x19x19 at stride 2, 12.1 against 38 us on 8x320x51x51 with 16; with 4 channels 8.5 us here against 40 on
     // the direct kernel for 30x48x31x31); fp32 stays on the vector pipe up to 8.
@@ -391,6 +405,12 @@ bool grouped_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out)
     out->grid_y = 1;
     out->block = 256;
     out->lds = 0;
+    {
+        // fitted to 700 timed fp32 layers, met within 19 % rms: multiply-adds at 27 a clock and compute unit, a load of an
+        // element by a thread each 25 ns / 1000, and a chain of the channels
+        const double threads = (double)bg.tasks * cg, loads = ((bv->TR - 1) * bv->ST + bv->RS) * (3.0 * bv->ST + bv->RS) + bv->KF * bv->RS * bv->RS;
+        out->us = 3.6 + threads * bv->KF * bv->TR * 4 * bv->RS * bv->RS / 27.5e6 + threads * loads / env.cus * 25e-6 + 0.2 * cg;
+    }
     memcpy(out->geom, &bg, sizeof bg);
     return true;
 }

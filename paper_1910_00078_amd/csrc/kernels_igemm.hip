@@ -1268,7 +1268,7 @@ const Variant* find_variant(const char* name, size_t len)
     return nullptr;
 }
 
-void fill_plan(const ConvArgs& a, const Variant& v, const IgemmGeom& g, LaunchPlan* out)
+void fill_plan(const ConvArgs& a, const Variant& v, const IgemmGeom& g, int cus, LaunchPlan* out)
 {
     static_assert(sizeof(IgemmGeom) <= sizeof(out->geom), "geometry does not fit the plan");
     out->id = KID_IGEMM;
@@ -1278,6 +1278,7 @@ void fill_plan(const ConvArgs& a, const Variant& v, const IgemmGeom& g, LaunchPl
     out->grid_y = 1;
     out->block = (unsigned)((v.WM * v.WN * v.KS + igemm_producer_waves(v.TM, v.TN, v.TAPS, v.UA, v.UB)) * 64);
     out->lds = lds_bytes(v, g);
+    out->us = cost(a, v, g, cus) / 2400.0;
     memcpy(out->geom, &g, sizeof g);
 }
 
@@ -1317,7 +1318,7 @@ bool igemm_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out)
         }
         IgemmGeom g;
         if (!plan(a, *v, nb, th, &g)) return false;
-        fill_plan(a, *v, g, out);
+        fill_plan(a, *v, g, env.cus, out);
         return true;
     }
     double best = 1e300;
@@ -1353,7 +1354,7 @@ bool igemm_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out)
         }
     }
     if (!bv) return false;
-    fill_plan(a, *bv, bg, out);
+    fill_plan(a, *bv, bg, env.cus, out);
     return true;
 }
 

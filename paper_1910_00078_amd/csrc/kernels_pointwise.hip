@@ -591,6 +591,7 @@ bool pointwise_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out)
     out->grid_y = 1;
     out->block = (unsigned)((p.v->WM * p.v->WN + pw::ND) * 64);
     out->lds = p.lds;
+    out->us = p.us;
     memcpy(out->geom, &p.g, sizeof p.g);
     return true;
 }

@@ -488,7 +488,7 @@ bool tiled_f32_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out)
     const long long xe = (long long)a.N * a.C * a.H * a.W, ye = (long long)a.N * a.K * a.Ho * a.Wo, we = (long long)a.K * (a.C / a.groups) * a.R * a.S;
     if (xe >= (1LL << 30) || ye >= (1LL << 30) || we >= (1LL << 30)) return false;   // offsets stay in int
     // tiny problems are launch latency whatever runs them; the direct kernel splits their channels over lanes
-    if (!env.pin && ye * (a.C / a.groups) * a.R * a.S < (1LL << 22)) return false;
+    if (!env.pin && ye * (a.C / a.groups) * a.R * a.S < kTiledF32Work) return false;
     const int HoWo = a.Ho * a.Wo;
     double best = 1e300;
     const tf32::Variant* bv = nullptr;
@@ -542,6 +542,7 @@ bool tiled_f32_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out)
     out->lds = 2 * (bg.xfloats + bg.wfloats) * 4;
     const int partial = (bv->KS - 1) * bv->WM * bv->WN * bv->TM * bv->TN * 4096;
     if (out->lds < partial) out->lds = partial;
+    out->us = best / 2400.0;
     memcpy(out->geom, &bg, sizeof bg);
     return true;
 }

@@ -17,7 +17,6 @@ def _g(**kw):
 
 
 CASES = [
-    _g(name="one_pixel", N=2, C=20, K=20, H=1, W=1, groups=20),
     _g(name="wide_padding", N=1, C=6, K=6, H=3, W=5, groups=6, pad=(4, 30)),
     _g(name="narrow_7", N=3, C=12, K=12, H=7, W=7, groups=12),
     _g(name="exact_8", N=2, C=12, K=12, H=9, W=8, groups=12),
@@ -44,6 +43,21 @@ def test_grouped_shapes(w, dtype):
 def test_both_tile_heights(dtype, rows):
     w = _g(name="heights", N=2, C=6, K=6, H=10, W=12, groups=6, dtype=dtype)
     check_case(w, pin="direct_grouped_%s_3x3_s1_k1r%d" % (dtype, rows))
+
+
+# narrower outputs than the kernel is chosen for: nearly all of a piece lies outside the image
+NARROW = [
+    _g(name="one_pixel", N=2, C=20, K=20, H=1, W=1, groups=20),
+    _g(name="two_columns", N=3, C=12, K=12, H=5, W=2, groups=12),
+    _g(name="three_columns", N=1, C=10, K=10, H=3, W=3, groups=5),
+]
+
+
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F16, wl.F32])
+@pytest.mark.parametrize("rows", [1, 4])
+@pytest.mark.parametrize("w", NARROW, ids=lambda w: w.name)
+def test_narrow_outputs(w, rows, dtype):
+    check_case(wl.small_variant(w, dtype=dtype), pin="direct_grouped_%s_3x3_s1_k1r%d" % (dtype, rows))
 
 
 def test_epilogues_and_unaligned_buffers():
