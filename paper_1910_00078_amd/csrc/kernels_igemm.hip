@@ -1251,8 +1251,12 @@ double cost(const ConvArgs& a, const Variant& v, const IgemmGeom& g, int cus)
     const double mfma = 32.0 * per_wave * v.TN * (a.R * a.S) * (v.CC / 16 / v.KS) * g.n_stages;
     // fixed launch/drain cost, a barrier hand-over per stage, and the fill of the first stage (which
     // nothing overlaps): smaller stages start the matrix pipe sooner
-    // (400 cycles), which with the producers' work takes 1500 whatever it multiplies
-    const double hand_over = mfma / g.n_stages + 400.0 < 1500.0 ? 1500.0 - mfma / g.n_stages : 400.0;
+    // (400 cycles), which with the producers' work takes 1500 whatever it multiplies -- and for 1x1, where nothing is
+    // long enough to hide it, 64 more for each 16-byte load of a thread where four producer waves load both operands (one
+    // block, C = 64 to 1024, us for 32 channels: eight producers 0.53, four 0.70 and 0.78)
+    const bool split = v.TAPS != 1 || igemm_producer_waves(v.TM, v.TN, v.TAPS, v.UA, v.UB) == 8;
+    const double least = 1500.0 + (split ? 0.0 : 64.0 * (8 * v.UA + v.UB)), mul = mfma / g.n_stages;
+    const double hand_over = mul + 400.0 < least ? least - mul : 400.0;
     const double overhead = 3000.0 + hand_over * g.n_stages + (g.xbytes + g.wbytes) / 16.0;
     // Filter sizes without a compiled transpose: their filters are gathered and scattered one element at a time, and their
     // multiply loop waits for every fragment (16x48x35x35 K=72 5x5 fp16: 37.9 us, against 18.5 us with one)

@@ -27,6 +27,9 @@ def _v(**kw):
     (_v(N=44, C=14, H=31, W=31, K=96, dtype=wl.F32), "tiled_f32_32x32"),
     # its chunk does not fit the 16-byte staging
     (_v(N=18, C=15, H=73, W=73, K=129, stride=(2, 2), dtype=wl.F32), "tiled_f32_128x32_c8"),
+    # stages of 64 channels by four producer waves, on lines too short for the pointwise kernel
+    (_v(N=5, C=521, H=7, W=7, K=48, R=1, S=1, pad=(0, 0), stride=(1, 2)), "igemm_512x64"),
+    (_v(N=16, C=41, H=1, W=1, K=640, R=1, S=1, pad=(0, 0), dtype=wl.F16), "igemm_512x64"),
     # outputs of a few pixels fill a corner of the grouped kernel's pieces
     (_v(N=14, C=168, H=1, W=1, K=10752, R=5, S=5, pad=(2, 2), groups=56), "direct_grouped"),
     (_v(N=16, C=1309, H=1, W=1, K=1309, R=5, S=5, pad=(2, 2), stride=(2, 2), groups=187), "direct_grouped"),
