@@ -30,6 +30,8 @@ def _v(**kw):
     # stages of 64 channels by four producer waves, on lines too short for the pointwise kernel
     (_v(N=5, C=521, H=7, W=7, K=48, R=1, S=1, pad=(0, 0), stride=(1, 2)), "igemm_512x64"),
     (_v(N=16, C=41, H=1, W=1, K=640, R=1, S=1, pad=(0, 0), dtype=wl.F16), "igemm_512x64"),
+    # few blocks of the wide tile with streamed filters on short runs of pixels
+    (_v(N=2, C=1712, H=40, W=40, K=27, R=1, S=1, pad=(0, 0), stride=(3, 1)), "igemm_lines_256x64_c32_r6_w"),
     # outputs of a few pixels fill a corner of the grouped kernel's pieces
     (_v(N=14, C=168, H=1, W=1, K=10752, R=5, S=5, pad=(2, 2), groups=56), "direct_grouped"),
     (_v(N=16, C=1309, H=1, W=1, K=1309, R=5, S=5, pad=(2, 2), stride=(2, 2), groups=187), "direct_grouped"),
