@@ -136,8 +136,8 @@ cvx_status_t cvx_activation_fwd(cvx_handle_t h, cvx_act_t act, float act_alpha,
 
 /* What the library would run for this problem, without running it (the find step of Sec. IV-A
  * reduced to its answer: algorithm name and the additional memory it needs -- always 0 here).
- * The answer is for 16-byte-aligned buffers; buffers that are only element-aligned are served by
- * the "direct_*" kernel.  cvx_get_last_kernel names what a compute call actually enqueued.  kernel_name receives a
+ * The answer is for 16-byte-aligned buffers; buffers that are only element-aligned are served, in the 16-bit
+ * types, by the "direct_*" or "grouped_*" kernel.  cvx_get_last_kernel names what a compute call actually enqueued.  kernel_name receives a
  * NUL-terminated string of at most name_cap bytes (may be NULL with name_cap 0). */
 cvx_status_t cvx_conv_fwd_query(cvx_tensor_desc_t xd, cvx_tensor_desc_t wd, cvx_conv_desc_t conv,
                                 cvx_tensor_desc_t yd, char* kernel_name, int name_cap,

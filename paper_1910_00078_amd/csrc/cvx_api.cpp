@@ -210,11 +210,11 @@ bool make_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out)
     if (env.policy == 0) {
         if (env.pin) {
             // the pin names one kernel of one family; nothing else may serve the call
-            if (strncmp(env.pin, "pointwise_", 10) == 0 || strncmp(env.pin, "igemm_lines_", 12) == 0) return pointwise_plan(a, env, out);
+            if (strncmp(env.pin, "pointwise_", 10) == 0) return pointwise_plan(a, env, out);
             if (strncmp(env.pin, "stem_", 5) == 0) return stem_plan(a, env, out);
             if (strncmp(env.pin, "igemm_", 6) == 0) return igemm_plan(a, env, out);
             if (strncmp(env.pin, "tiled_f32_", 10) == 0) return tiled_f32_plan(a, env, out);
-            if (strncmp(env.pin, "direct_grouped_", 15) == 0) return grouped_plan(a, env, out);
+            if (strncmp(env.pin, "grouped_", 8) == 0) return grouped_plan(a, env, out);
             if (strncmp(env.pin, "direct", 6) == 0) return direct_plan(a, env, out);
             return false;
         }

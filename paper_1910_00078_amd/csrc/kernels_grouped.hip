@@ -314,12 +314,12 @@ struct Variant {
 };
 
 #define GRP_VARIANT(RS, ST, KF, TR)                                                                                              \
-    {{"direct_grouped_f32_" #RS "x" #RS "_s" #ST "_k" #KF "r" #TR, "direct_grouped_f16_" #RS "x" #RS "_s" #ST "_k" #KF "r" #TR,                  \
-      "direct_grouped_bf16_" #RS "x" #RS "_s" #ST "_k" #KF "r" #TR},                                                                     \
+    {{"grouped_f32_" #RS "x" #RS "_s" #ST "_k" #KF "r" #TR, "grouped_f16_" #RS "x" #RS "_s" #ST "_k" #KF "r" #TR,                  \
+      "grouped_bf16_" #RS "x" #RS "_s" #ST "_k" #KF "r" #TR},                                                                     \
      RS, ST, KF, TR,                                                                                                             \
      {grouped_kernel<DT_F32, RS, ST, KF, TR>, grouped_kernel<DT_F16, RS, ST, KF, TR>, grouped_kernel<DT_BF16, RS, ST, KF, TR>}}
 
-// name: direct_grouped_<type>_<filter>_s<stride>_k<filters per thread>r<rows per thread>; for each filter and stride the larger
+// name: grouped_<type>_<filter>_s<stride>_k<filters per thread>r<rows per thread>; for each filter and stride the larger
 // register tiles first
 const Variant kVariants[] = {
     GRP_VARIANT(3, 1, 4, 2), GRP_VARIANT(3, 1, 4, 1), GRP_VARIANT(3, 1, 1, 4), GRP_VARIANT(3, 1, 1, 2), GRP_VARIANT(3, 1, 1, 1),

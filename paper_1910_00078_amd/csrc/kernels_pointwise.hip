@@ -443,18 +443,18 @@ constexpr int LDS_LIMIT = 160 * 1024;
 
 struct Variant {
     const char* name;                          // on whole images of aligned chunks
-    const char* line_name;                     // on other lines: an implicit GEMM over chunks of them
+    const char* line_name;                     // on other lines
     int WM, WN, TM, TN, CC, NS;
     bool ws;                                   // filters streamed
     void (*kern[2][2])(ConvArgs, Geom);        // [fp16][column stride 2]
 };
 
 #define PW_VARIANT(nm, WM, WN, TM, TN, CC, NS, WS)                                              \
-    {"pointwise_" nm, "igemm_lines_" nm, WM, WN, TM, TN, CC, NS, WS,                                                            \
+    {"pointwise_" nm, "pointwise_lines_" nm, WM, WN, TM, TN, CC, NS, WS,                                                            \
      {{pointwise_kernel<DT_BF16, WM, WN, TM, TN, CC, NS, 1, WS>, pointwise_kernel<DT_BF16, WM, WN, TM, TN, CC, NS, 2, WS>}, \
       {pointwise_kernel<DT_F16, WM, WN, TM, TN, CC, NS, 1, WS>, pointwise_kernel<DT_F16, WM, WN, TM, TN, CC, NS, 2, WS>}}}
 
-// name: pointwise_ or igemm_lines_<pixels per tile>x<filters per block>_c<channels per stage>_r<ring slots>[_w: filters streamed]
+// name: pointwise_ or pointwise_lines_<pixels per tile>x<filters per block>_c<channels per stage>_r<ring slots>[_w: filters streamed]
 const Variant kVariants[] = {
     PW_VARIANT("256x64_c32_r5", 4, 1, 2, 2, 32, 5, false),
     PW_VARIANT("256x64_c32_r3", 4, 1, 2, 2, 32, 3, false),

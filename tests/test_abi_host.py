@@ -171,10 +171,21 @@ def test_kernel_choice_is_host_logic_and_follows_the_shape():
         assert family(wl.WORKLOADS[name]).startswith(prefix), name
     v = wl.small_variant
     assert family(v(wl.WORKLOADS["c4"], K=96)).startswith("stem_256x64")            # K > 64: the general stem kernel
-    assert family(v(wl.WORKLOADS["c3a"], stride=(2, 2))).startswith("igemm_")        # strided 1x1 is not pointwise
-    assert family(v(wl.WORKLOADS["c3a"], H=7, W=7)).startswith("igemm_")             # 49 pixels: not a multiple of 8
+    # 1x1 on lines of at least 8 pixels is pointwise, with a column stride up to 2 and any channel count from 8 on;
+    # shorter lines, wider strides, padding and groups are the implicit GEMM's
+    c3a = wl.WORKLOADS["c3a"]
+    assert family(v(c3a, stride=(2, 2))).startswith("pointwise_lines_")
+    assert family(v(c3a, H=7, W=7)).startswith("pointwise_lines_")                   # 49 pixels: not a multiple of 8
+    assert family(v(c3a, C=9)).startswith("pointwise_2")                             # 3136 pixels: one
+    assert family(v(c3a, H=8, W=8, stride=(2, 2))).startswith("pointwise_lines_")
+    assert family(v(c3a, H=7, W=7, stride=(2, 2))).startswith("igemm_")              # rows of 7
+    assert family(v(c3a, H=1, W=7)).startswith("igemm_")                             # a plane of 7
+    assert family(v(c3a, stride=(1, 3))).startswith("igemm_")
+    assert family(v(c3a, pad=(1, 1))).startswith("igemm_")
+    assert family(v(c3a, groups=4)).startswith("igemm_")
     assert family(v(wl.WORKLOADS["c2"], C=128, K=128, groups=4)).startswith("igemm_")
-    assert family(v(wl.WORKLOADS["c2"], C=64, K=64, groups=64)).startswith("direct_")  # depthwise
+    assert family(v(wl.WORKLOADS["c2"], C=64, K=64, groups=64)).startswith("grouped_")  # depthwise
+    assert family(v(wl.WORKLOADS["c2"], C=64, K=64, groups=64, dil=(2, 2), pad=(2, 2))).startswith("direct_")
     assert family(v(wl.WORKLOADS["c2"], dtype=wl.F32)).startswith("tiled_f32_")         # fp32 of a real size: the fp32 MFMA kernel
     assert family(v(wl.WORKLOADS["c4"], dtype=wl.F32)).startswith("tiled_f32_")         # any filter size
 

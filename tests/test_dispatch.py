@@ -31,17 +31,17 @@ def _v(**kw):
     (_v(N=5, C=521, H=7, W=7, K=48, R=1, S=1, pad=(0, 0), stride=(1, 2)), "igemm_512x64"),
     (_v(N=16, C=41, H=1, W=1, K=640, R=1, S=1, pad=(0, 0), dtype=wl.F16), "igemm_512x64"),
     # few blocks of the wide tile with streamed filters on short runs of pixels
-    (_v(N=2, C=1712, H=40, W=40, K=27, R=1, S=1, pad=(0, 0), stride=(3, 1)), "igemm_lines_256x64_c32_r6_w"),
+    (_v(N=2, C=1712, H=40, W=40, K=27, R=1, S=1, pad=(0, 0), stride=(3, 1)), "pointwise_lines_256x64_c32_r6_w"),
     # outputs of a few pixels fill a corner of the grouped kernel's pieces
-    (_v(N=14, C=168, H=1, W=1, K=10752, R=5, S=5, pad=(2, 2), groups=56), "direct_grouped"),
-    (_v(N=16, C=1309, H=1, W=1, K=1309, R=5, S=5, pad=(2, 2), stride=(2, 2), groups=187), "direct_grouped"),
-    (_v(N=9, C=126, H=3, W=3, K=126, stride=(2, 2), groups=126), "direct_grouped"),
-    (_v(N=7, C=58, H=1, W=1, K=58, groups=29, dtype=wl.F32), "direct_grouped"),
+    (_v(N=14, C=168, H=1, W=1, K=10752, R=5, S=5, pad=(2, 2), groups=56), "grouped"),
+    (_v(N=16, C=1309, H=1, W=1, K=1309, R=5, S=5, pad=(2, 2), stride=(2, 2), groups=187), "grouped"),
+    (_v(N=9, C=126, H=3, W=3, K=126, stride=(2, 2), groups=126), "grouped"),
+    (_v(N=7, C=58, H=1, W=1, K=58, groups=29, dtype=wl.F32), "grouped"),
     # small enough for the direct kernel to deal the channels over lanes
-    (_v(N=4, C=40, H=17, W=17, K=40, stride=(2, 2), groups=5, dtype=wl.F32), "direct_grouped"),
+    (_v(N=4, C=40, H=17, W=17, K=40, stride=(2, 2), groups=5, dtype=wl.F32), "grouped"),
     # many filters per group in fp32: the matrix pipe, which reads the input once for 32 of them and more
-    (_v(N=24, C=336, H=9, W=9, K=2688, R=5, S=5, pad=(2, 2), stride=(2, 2), groups=42, dtype=wl.F32), "direct_grouped"),
-    (_v(N=27, C=320, H=6, W=6, K=20480, groups=40, dtype=wl.F32), "direct_grouped"),
+    (_v(N=24, C=336, H=9, W=9, K=2688, R=5, S=5, pad=(2, 2), stride=(2, 2), groups=42, dtype=wl.F32), "grouped"),
+    (_v(N=27, C=320, H=6, W=6, K=20480, groups=40, dtype=wl.F32), "grouped"),
 ], ids=lambda v: getattr(v, "name", v))
 def test_measured_slower_elsewhere(w, slow):
     assert not kernel(w).startswith(slow)
@@ -52,4 +52,4 @@ def test_measured_slower_elsewhere(w, slow):
     _v(N=8, C=64, H=28, W=28, K=64, groups=8, dtype=wl.F32), _v(N=8, C=32, H=14, W=14, K=32, R=5, S=5, pad=(2, 2), groups=8, dtype=wl.F32),
 ], ids=lambda w: "%s_c%d_h%d" % (w.dtype, w.C, w.H))
 def test_few_channels_per_group_keep_their_kernel(w):
-    assert kernel(w).startswith("direct_grouped")
+    assert kernel(w).startswith("grouped")

@@ -35,14 +35,14 @@ CASES = [
 @pytest.mark.parametrize("dtype", [wl.BF16, wl.F16, wl.F32])
 @pytest.mark.parametrize("w", CASES, ids=lambda w: w.name)
 def test_grouped_shapes(w, dtype):
-    assert check_case(wl.small_variant(w, dtype=dtype)).startswith("direct_grouped_")
+    assert check_case(wl.small_variant(w, dtype=dtype)).startswith("grouped_")
 
 
 @pytest.mark.parametrize("dtype", [wl.BF16, wl.F16, wl.F32])
 @pytest.mark.parametrize("rows", [1, 4])
 def test_both_tile_heights(dtype, rows):
     w = _g(name="heights", N=2, C=6, K=6, H=10, W=12, groups=6, dtype=dtype)
-    check_case(w, pin="direct_grouped_%s_3x3_s1_k1r%d" % (dtype, rows))
+    check_case(w, pin="grouped_%s_3x3_s1_k1r%d" % (dtype, rows))
 
 
 # narrower outputs than the kernel is chosen for: nearly all of a piece lies outside the image
@@ -57,7 +57,7 @@ NARROW = [
 @pytest.mark.parametrize("rows", [1, 4])
 @pytest.mark.parametrize("w", NARROW, ids=lambda w: w.name)
 def test_narrow_outputs(w, rows, dtype):
-    check_case(wl.small_variant(w, dtype=dtype), pin="direct_grouped_%s_3x3_s1_k1r%d" % (dtype, rows))
+    check_case(wl.small_variant(w, dtype=dtype), pin="grouped_%s_3x3_s1_k1r%d" % (dtype, rows))
 
 
 def test_epilogues_and_unaligned_buffers():
@@ -71,7 +71,7 @@ def test_epilogues_and_unaligned_buffers():
     check_case(w, use_bias=False)
     check_case(w, bias_f32=True)
     for off in [(1, 0, 0), (0, 1, 0), (0, 0, 1)]:
-        assert check_case(w, offsets=off).startswith("direct_grouped_")
+        assert check_case(w, offsets=off).startswith("grouped_")
 
 
 INF = {wl.BF16: 0x7f80, wl.F16: np.float16(np.inf), wl.F32: np.float32(np.inf)}
