@@ -1080,6 +1080,22 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
     template __global__ void igemm_kernel<DT_BF16, WM, WN, TM, TN, CC, TAPS, UA, UB, KS, true>(ConvArgs, IgemmGeom);  \
     template __global__ void igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, KS, false>(ConvArgs, IgemmGeom);  \
     template __global__ void igemm_kernel<DT_F16, WM, WN, TM, TN, CC, TAPS, UA, UB, KS, true>(ConvArgs, IgemmGeom);
+#ifdef CVX_PHASE_TRACE
+// The stamps' address is a variable of each object: every part sets its own (here), the base object calls them all.
+#define IGEMM_TRACE_PARTS(X) X(1) X(2) X(3) X(4) X(5) X(6) X(7) X(8) X(9)
+#define IGEMM_TRACE_SETTER_(n) cvx_igemm_set_phase_trace_##n
+#define IGEMM_TRACE_SETTER(n) IGEMM_TRACE_SETTER_(n)
+#ifdef CVX_PART
+hipError_t IGEMM_TRACE_SETTER(CVX_PART)(unsigned long long* device_buffer)
+{
+    return hipMemcpyToSymbol(HIP_SYMBOL(g_phase_trace), &device_buffer, sizeof(device_buffer));
+}
+#else
+#define IGEMM_TRACE_DECLARE(n) hipError_t IGEMM_TRACE_SETTER(n)(unsigned long long*);
+IGEMM_TRACE_PARTS(IGEMM_TRACE_DECLARE)
+#endif
+#endif
+
 #if CVX_PART == 1
 IGEMM_PART_1(IGEMM_INSTANTIATE)
 #elif CVX_PART == 2
@@ -1291,7 +1307,10 @@ void fill_plan(const ConvArgs& a, const Variant& v, const IgemmGeom& g, int cus,
 #ifdef CVX_PHASE_TRACE
 extern "C" int cvx_debug_set_phase_trace(unsigned long long* device_buffer)
 {
-    return (int)hipMemcpyToSymbol(HIP_SYMBOL(g_phase_trace), &device_buffer, sizeof(device_buffer));
+    hipError_t e = hipSuccess;
+#define IGEMM_TRACE_CALL(n) if (e == hipSuccess) e = IGEMM_TRACE_SETTER(n)(device_buffer);
+    IGEMM_TRACE_PARTS(IGEMM_TRACE_CALL)
+    return (int)e;
 }
 #endif
 
