@@ -349,12 +349,14 @@ def conv_fwd_fused(x, w, bias=None, *, pad=0, stride=1, dil=1, groups=1, act=CVX
         raise ValueError("bias must be a contiguous GPU tensor")
     bias_ch = None if bias is None else bias.numel()
     args = (dt, tuple(x.shape), tuple(w.shape), _pair(pad), _pair(stride), _pair(dil), groups, bias_dt, hip_stream, bias_ch)
-    if pin or policy:
+    own = bool(pin) or policy != 0 or type(policy) is not int
+    if own:
         plan = ConvPlan(*args)          # developer choices of a kernel are for this call alone
     else:
-        plan = _per_thread.plans.get((device,) + args, args)
+        # the type of `groups` is part of the key: 1.0 equals 1, but no plan is made for it
+        plan = _per_thread.plans.get((device, type(groups)) + args, args)
     try:
-        if pin or policy:
+        if own:
             cvx_set_kernel_policy(plan.h, policy)
             plan.pin(pin)
         if out is None:
@@ -373,6 +375,6 @@ def conv_fwd_fused(x, w, bias=None, *, pad=0, stride=1, dil=1, groups=1, act=CVX
         if info is not None:
             info["kernel"] = plan.last_kernel()
     finally:
-        if pin or policy:
+        if own:
             plan.close()
     return y

@@ -1,6 +1,9 @@
 """The plans conv_fwd_fused keeps between calls: reused for a repeated problem, bounded, closed on
 eviction and when their thread ends (host only: plans are host objects)."""
+import ctypes
 import threading
+
+import pytest
 
 from paper_1910_00078_amd import cvx
 
@@ -34,3 +37,16 @@ def test_a_threads_plans_are_its_own_and_are_closed_with_it():
     mine = cvx._per_thread.plans.get(_args(8), _args(8))
     assert mine is not seen[0]
     assert seen[0].h is None
+
+
+@pytest.mark.gpu
+def test_what_no_plan_is_made_for_finds_none():
+    """Arguments that equal a kept problem's without being of its types are refused before and after it is kept."""
+    import torch
+    x, w = (torch.zeros(shape, dtype=torch.bfloat16, device="cuda") for shape in ((1, 8, 6, 6), (4, 8, 3, 3)))
+    for _ in range(2):
+        for wrong in (dict(groups=1.0), dict(policy=0.0), dict(policy=None)):
+            with pytest.raises(ctypes.ArgumentError):
+                cvx.conv_fwd_fused(x, w, pad=1, **wrong)
+        assert cvx.conv_fwd_fused(x, w, pad=1).shape == (1, 4, 6, 6)
+        assert cvx.conv_fwd_fused(x, w, pad=1, groups=True, policy=False).shape == (1, 4, 6, 6)
