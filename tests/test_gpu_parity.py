@@ -63,7 +63,7 @@ def test_buffers_that_are_only_element_aligned(base, which):
 @pytest.mark.parametrize("which", ["x", "w", "y"])
 def test_fp32_buffers_that_are_only_element_aligned(which):
     """fp32 data one element off a 16-byte boundary stays on the matrix-instruction kernel, which then
-    stages its chunks element by element instead of in 16-byte pieces."""
+    stages its chunks in 16-byte pieces that start at any element."""
     w = wl.small_variant(wl.WORKLOADS["c2"], N=2, H=28, W=28, C=24, K=40, dtype=wl.F32)
     off = tuple(1 if which == n else 0 for n in "xwy")
     assert check_case(w, offsets=off).startswith("tiled_f32_")

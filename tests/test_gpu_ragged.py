@@ -1,9 +1,11 @@
 """Implicit-GEMM kernels on channel and filter counts that fill neither a stage nor a filter block, against
 the oracle: one channel past an octet, past a stage, past a half stage; one filter past a block, one short of
 it; the same inside groups, where what follows a group's channels is the next group's data."""
+import numpy as np
 import pytest
 
 import workloads as wl
+from parity import run_gpu
 from test_gpu_parity import check_case
 
 pytestmark = pytest.mark.gpu
@@ -87,3 +89,32 @@ def test_split_5x5(C):
                                     (_c(name="groups", N=2, C=120, K=66, H=7, W=7, groups=3), "1,7")], ids=lambda v: getattr(v, "name", None))
 def test_split_reduction(variant, w, tile, dtype):
     check_case(wl.small_variant(w, dtype=dtype), pin=variant + "," + tile)
+
+
+@pytest.mark.parametrize("pin", ["igemm_256x64_c16_3x3,1,9", "igemm_256x64_c32_3x3,1,9", "igemm_512x64_c16_3x3,1,9", "igemm_64x32_c64_3x3,1,4",
+                                 "igemm_256x64_c16_5x5,1,9", "igemm_64x32_c32_5x5,1,4", "igemm_256x64_c16_7,1,9", "igemm_64x32_c64_7,1,4",
+                                 "igemm_256x64_c64_1x1,1,9", "igemm_512x64_c32_1x1,1,9", "igemm_256x64_c16_any,1,9"])
+def test_infinite_neighbours_stay_out(pin):
+    """What is read past a group's channels or a tensor's end must not reach the sum: an infinity in the next group, image or
+    filter would turn it into a NaN."""
+    R, S = (5, 5) if "5x5" in pin else (7, 1) if "_7" in pin else (1, 1) if "1x1" in pin else (3, 3)
+    if "any" in pin:
+        R, S = 2, 3
+    w = _c(name="inf", N=2, C=78, K=42, H=9, W=9, R=R, S=S, pad=(R // 2, S // 2), groups=2)
+    if "any" in pin:
+        w = wl.small_variant(w, H=10, pad=(0, 1))
+    x, wt, b = wl.make_inputs(w)
+    clean, _ = run_gpu(w, x, wt, b, pin=pin)
+    x, wt = x.copy(), wt.copy()
+    inf = 0x7f80                                        # bf16
+    x[1] = inf
+    x[0, 39:] = inf
+    wt[1:] = inf
+    got, _ = run_gpu(w, x, wt, b, pin=pin)
+    np.testing.assert_array_equal(got[0, 0], clean[0, 0])
+    x2 = x.copy()
+    x2[:] = inf
+    x2[1, 39:], wt2 = wl.make_inputs(w)[0][1, 39:], wt.copy()
+    wt2[:41], wt2[41] = inf, wl.make_inputs(w)[1][41]
+    got, _ = run_gpu(w, x2, wt2, b, pin=pin)            # the last image, group and filter, at the tensors' ends
+    np.testing.assert_array_equal(got[1, 41], clean[1, 41])
