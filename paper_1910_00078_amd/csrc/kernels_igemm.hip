@@ -133,7 +133,7 @@ __host__ __device__ constexpr int igemm_filter_octet_pitch(int KT, int OCT)
 // the epilogue.  Small problems (one image, few pixels) leave most of the chip idle and are bound by the chain of
 // stages, each a load latency, a transpose and a hand-over of about 0.8 us however little it multiplies; a small tile
 // with 64 channels a stage has more blocks and a half to a quarter of the stages, and splitting them over waves
-// keeps their multiply time below the producers'.  1x256x14x14 K=256: 256x64 tiles with 32 channels 17.4 us, this 8.6.
+// keeps their multiply time below the producers'.  1x256x14x14 K=256: 256x64 tiles with 32 channels 18.0 us, this 8.2.
 template <int DT, int WM, int WN, int TM, int TN, int CC, int TAPS, int UA, int UB, int KS, bool RAGGED>
 __global__ void __launch_bounds__((WM * WN * KS + igemm_producer_waves(TM, TN, TAPS, UA, UB)) * 64)
 igemm_kernel(ConvArgs a, IgemmGeom g)

@@ -27,9 +27,10 @@
 //                       store.
 //   Chunks              the pixel axis is cut into chunks of 8 input pixels that lie in one line (a line is
 //                       an image, or one needed image row under a stride).  A line's last chunk is moved back
-//                       to end with the line, so no load leaves the tensor and no size is refused: its pixels
-//                       are computed twice, with the same result.  Chunks then start at any 2-byte address,
-//                       which the direct-to-LDS loads take at a lower rate that is still above device memory's.
+//                       to end with the line, so no load leaves the tensor: its pixels are computed twice,
+//                       with the same result.  Chunks then start at any 2-byte address, which the direct-to-LDS
+//                       loads take at a lower rate that is still above device memory's.  Lines shorter than a
+//                       chunk are left to the implicit-GEMM kernel.
 //   Column stride 2     whole chunks are loaded (their lines are fetched anyway) and multiplied; the epilogue
 //                       drops the odd columns.  Twice the matrix work is still below the memory time: against
 //                       the implicit-GEMM kernel, which transposed both halves in registers,

@@ -114,7 +114,8 @@ def test_igemm_1x1(variant, w, dtype):
 
 
 @pytest.mark.parametrize("w", [_v("c3a", name="padded", N=2, C=64, K=40, H=28, W=28, pad=(1, 1)), _v("c3a", name="groups4", N=8, C=256, K=64, H=28, W=28, groups=4),
-                               _v("c3a", name="plane7", N=40, C=128, K=64, H=1, W=7)], ids=lambda w: w.name)
+                               _v("c3a", name="plane7", N=40, C=128, K=64, H=1, W=7),
+                               _v("c3a", name="w7_s2", N=9, C=72, K=64, H=9, W=7, stride=(2, 2))], ids=lambda w: w.name)
 def test_layers_past_the_pointwise_kernels_bounds(w):
     assert check_case(w).startswith("igemm_")
 
