@@ -368,7 +368,7 @@ bool grouped_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out)
     const long long work = (long long)a.N * a.K * a.Ho * a.Wo * cg * a.R * a.S;
     const bool direct_instead = a.dtype != DT_F32 || work < kTiledF32Work;    // else the tiled fp32 kernel
     const bool unit3 = a.stride_h == 1 && a.R == 3;
-    const int few = a.dtype == DT_F32 || a.Wo >= 4 ? 1 : a.Wo == 3 ? (a.stride_h == 1 || a.R == 5 ? 1 : 3) : unit3 ? 2 : 4;
+    const int few = a.dtype == DT_F32 || a.Wo >= 4 ? 1 : a.Wo == 3 ? (a.stride_h == 1 || a.R == 5 ? 1 : 3) : unit3 ? 2 : 3;
     const bool one = a.Wo == 1 && !(a.dtype == DT_F32 && a.W > 1 && (a.R == 3 || !direct_instead));
     if (!env.pin && (one || cg < few)) return false;
     // The direct kernel deals the channels of small problems over lanes from 8 on (4x40x17x17, 5 groups, stride 2: 4.4 us
