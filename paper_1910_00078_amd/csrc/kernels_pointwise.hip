@@ -524,8 +524,9 @@ bool plan_variant(const ConvArgs& a, const Variant& v, int cus, Plan* out)
     const double rate = 5500.0 / resident < 64.0 ? 5500.0 / resident : 64.0;        // KB per us and block, device memory
     const double x_kb = (double)g.stages_per_tile * stage / 1024.0, y_kb = (double)PT / SW * (a.K < KT ? a.K : KT) * 2 / 1024.0;
     // Few blocks of the wide streamed tile are chains of load latencies, twice as long where its pixels come in short runs:
-    // 2x1712x40x40 K=27 stride (3, 1), 54 stages: 46.4 us, in 128x128 tiles 28.5
-    const bool chain = v.ws && PT == 256 && resident < cus / 2 && (a.stride_h > 1 ? a.W : g.HW) < 64;
+    // 2x1712x40x40 K=27 stride (3, 1), 54 stages: 46.4 us, in 128x128 tiles 28.5; with many filter blocks the input comes
+    // from L2 (2x1232x32x32 K=1472 stride (3, 1): 19.2, in 128x32 tiles 33.4)
+    const bool chain = v.ws && PT == 256 && g.kblocks <= 4 && resident < cus / 2 && (a.stride_h > 1 ? a.W : g.HW) < 64;
     const double t_mem = (x_kb * (0.5 + 0.5 / g.kblocks) + y_kb) / rate, t_l2 = (x_kb / (g.y_aligned ? 64.0 : 45.0) + g.stages_per_tile * wstage / 1024.0 / 20.0) * (chain ? 2.0 : 1.0);
     const double t_mul = g.stages_per_tile * (v.CC / 16 * v.TM * v.TN * 32 / 0.6 + 250.0) / 2000.0 + 0.5 * v.TM * v.TN / 4;
     double tile = t_mem > t_l2 ? t_mem : t_l2;
