@@ -370,7 +370,6 @@ bool grouped_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out)
     const bool unit3 = a.stride_h == 1 && a.R == 3;
     const int few = a.dtype == DT_F32 || a.Wo >= 4 ? 1 : a.Wo == 3 ? (a.stride_h == 1 || a.R == 5 ? 1 : 3) : unit3 ? 2 : 3;
     const bool one = a.Wo == 1 && !(a.dtype == DT_F32 && a.W > 1 && (a.R == 3 || !direct_instead));
-    if (!env.pin && (one || cg < few)) return false;
     // The direct kernel deals the channels of small problems over lanes from 8 on (4x40x17x17, 5 groups, stride 2: 4.4 us
     // there, 6.2 here).
     if (!env.pin && cg >= 8 && direct_instead && (long long)a.N * a.K * a.Ho * a.Wo <= kDirectSplitOutputs) return false;
@@ -398,6 +397,10 @@ bool grouped_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out)
         bg = g;
     }
     if (!bv) return false;
+    // (tiles of four filters, which only large problems run, gain from width 2 on whatever the channels, 1.1-3x over 8 drawn
+    // layers, and with 6 channels of two pixels: 17x2128x2x2 K=34048 3x3 stride 2 40.5 us, 71.5 direct)
+    const bool four = bv->KF == 4 && (a.Wo > 1 || (a.W > 1 && cg >= 6));
+    if (!env.pin && !four && (one || cg < few)) return false;
     out->id = KID_GROUPED;
     out->name = bv->name[a.dtype];
     out->variant = (int)(bv - grp::kVariants);
