@@ -64,13 +64,14 @@ struct IgemmGeom {
 
 // 16-byte load of 8 consecutive 16-bit elements starting at element offset `off` of a tensor with
 // `total` elements (at least 8); elements outside the tensor read as zero.  Addresses are only 2-byte aligned.
-// A piece that reaches over an end of the tensor is read from where it fits and shifted into place; read one element
+// A piece that reaches over an end of the tensor is read from where it fits and shifted into place (not if it is not
+// wanted: any values do then, and nothing waits for them); read one element
 // after another, such pieces in the first and last blocks held up every launch (2x9x44x55 K=80 3x3 11.4 us, now 7.7).
-__device__ __forceinline__ u32x4 load8(const uint16_t* base, long long off, long long total)
+__device__ __forceinline__ u32x4 load8(const uint16_t* base, long long off, long long total, bool wanted = true)
 {
     const long long at = min(max(off, 0LL), total - 8);
     u32x4 v = *(const u32x4_a2*)(base + at);
-    if (off != at) {
+    if (off != at && wanted) {
         const long long by = off - at;                                // elements it was moved by
         const int s = 16 * (int)(by < 0 ? max(by, -8LL) + 8 : min(by, 8LL));   // of 256 bits: [v : 0] for an early piece, [0 : v] for a late one
         const uint64_t lo = (uint64_t)v[1] << 32 | v[0], hi = (uint64_t)v[3] << 32 | v[2];
@@ -272,8 +273,7 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
 #pragma unroll
             for (int u = 0; u < UA; ++u) {
                 if (a_oct[u] >= 0) {
-                    // channels past the group's end are whatever follows (store_stage clears them), and where that could
-                    // leave the tensor they are not read
+                    // channels past the group's end are whatever follows, or the tensor's last (store_stage clears them)
                     const int live = RAGGED ? g.cg - (cbase + a_oct[u] * 8) : 8;
                     const long long off0 = a_goff[u] + (long long)cbase * HW;
                     if (live > 0 && off0 >= 0 && off0 + 7LL * HW + 8 <= x_total) {
@@ -281,8 +281,7 @@ igemm_kernel(ConvArgs a, IgemmGeom g)
                         for (int j = 0; j < 8; ++j) ra[u][j] = *(const u32x4_a2*)(xg + off0 + (long long)j * HW);
                     } else if (live > 0) {
 #pragma unroll
-                        for (int j = 0; j < 8; ++j)
-                            if (!RAGGED || j < live) ra[u][j] = load8(xg, off0 + (long long)j * HW, x_total);
+                        for (int j = 0; j < 8; ++j) ra[u][j] = load8(xg, off0 + (long long)j * HW, x_total, !RAGGED || j < live);
                     }
                 }
             }
