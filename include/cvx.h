@@ -153,6 +153,10 @@ cvx_status_t cvx_get_last_kernel(cvx_handle_t h, char* kernel_name, int name_cap
  * CVX_ERR_UNSUPPORTED if it cannot run the problem; NULL or "" removes the pin. */
 cvx_status_t cvx_set_kernel_policy(cvx_handle_t h, int policy);
 cvx_status_t cvx_debug_pin_kernel(cvx_handle_t h, const char* spec);
+/* How many bytes past the ends of x and w (or before their starts) any load of kernel `spec` (the "tiled_f32_split_*" ones)
+ * reaches for this problem, computed on the host as the kernel computes it: 0 or less where all stay inside. */
+cvx_status_t cvx_debug_reads_past_end(cvx_tensor_desc_t xd, cvx_tensor_desc_t wd, cvx_conv_desc_t conv, cvx_tensor_desc_t yd,
+                                      const char* spec, long long* x_past, long long* w_past);
 
 const char* cvx_status_string(cvx_status_t s);
 const char* cvx_last_error(void);   /* thread-local detail of the last failing call; never NULL */

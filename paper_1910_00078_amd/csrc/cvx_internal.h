@@ -98,6 +98,8 @@ bool tiled_f32_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out);
 hipError_t tiled_f32_launch(const ConvArgs& a, const LaunchPlan& p, hipStream_t s);
 bool split_f32_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out);
 hipError_t split_f32_launch(const ConvArgs& a, const LaunchPlan& p, hipStream_t s);
+// How far the loads of a planned launch reach past the ends of x and w, in bytes (0 or less: they stay inside).
+void split_f32_reads(const ConvArgs& a, const LaunchPlan& p, long long past[2]);
 bool grouped_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out);
 hipError_t grouped_launch(const ConvArgs& a, const LaunchPlan& p, hipStream_t s);
 bool direct_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out);

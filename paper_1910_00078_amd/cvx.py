@@ -29,7 +29,7 @@ EXPORTS = [
     "cvx_conv_desc_destroy", "cvx_conv_fwd_output_dim",
     "cvx_conv_fwd", "cvx_conv_fwd_fused", "cvx_conv_fwd_fused_bn",
     "cvx_bias_add", "cvx_activation_fwd", "cvx_conv_fwd_query", "cvx_get_last_kernel", "cvx_set_kernel_policy",
-    "cvx_debug_pin_kernel",
+    "cvx_debug_pin_kernel", "cvx_debug_reads_past_end",
     "cvx_status_string", "cvx_last_error",
 ]
 
@@ -69,6 +69,7 @@ def lib():
             "cvx_set_kernel_policy": [vp, ci],
             "cvx_get_last_kernel": [vp, ctypes.c_char_p, ci],
             "cvx_debug_pin_kernel": [vp, ctypes.c_char_p],
+            "cvx_debug_reads_past_end": [vp, vp, vp, vp, ctypes.c_char_p, ctypes.POINTER(ctypes.c_longlong), ctypes.POINTER(ctypes.c_longlong)],
         }
         for name, args in sig.items():
             f = getattr(L, name)
@@ -132,6 +133,12 @@ def cvx_get_last_kernel(h: int) -> str:
 
 def cvx_debug_pin_kernel(h: int, spec: Optional[str]) -> None:
     _check(lib().cvx_debug_pin_kernel(h, spec.encode() if spec else None), "cvx_debug_pin_kernel")
+
+
+def cvx_debug_reads_past_end(xd: int, wd: int, conv: int, yd: int, spec: str) -> Tuple[int, int]:
+    x, w = ctypes.c_longlong(), ctypes.c_longlong()
+    _check(lib().cvx_debug_reads_past_end(xd, wd, conv, yd, spec.encode(), ctypes.byref(x), ctypes.byref(w)), "cvx_debug_reads_past_end")
+    return x.value, w.value
 
 
 def cvx_tensor_desc_create() -> int:
