@@ -1,9 +1,10 @@
-"""fp32 layers on the bf16 matrix pipe at the ends of fp32's range: results next to the largest value."""
+"""fp32 layers on the bf16 matrix pipe at the ends of fp32's range: results next to the largest value, and values next to the
+smallest, whose parts would fall below bf16's smallest exponent."""
 import numpy as np
 import pytest
 
 import workloads as wl
-from parity import run_gpu
+from parity import run_gpu, run_oracle
 from test_gpu_split_f32 import _c, _s1
 
 pytestmark = pytest.mark.gpu
@@ -29,3 +30,18 @@ def test_products_next_to_the_largest_value(w, pin, value):
         square = float(np.float32(value) * np.float32(value))
     assert got[0, 0, 4, 4] == square and got[-1, 0, 2, 5] == -square and got[0, 5, 4, 4] == float(np.float32(value))
     assert not np.isnan(got).any()
+
+
+@pytest.mark.parametrize("w,pin", LAYERS, **IDS)
+@pytest.mark.parametrize("small,power", [("x", -112), ("x", -119), ("x", -124), ("w", -112), ("w", -119), ("w", -124), ("x", -136), ("w", -136)])
+def test_small_values_keep_their_bits(w, pin, small, power):
+    """One operand around 2^power, the other so large that results are ordinary.  32-bit sums in any order stay below 1e-6 here
+    (the fp32 matrix pipe's error is 3e-7 to 1e-7); below 2^-126 fp32 itself has fewer bits, which the stored inputs already are."""
+    x, wt, _ = wl.make_inputs(w)
+    x, wt = (np.ldexp(x, power if small == "x" else 100).astype(np.float32), np.ldexp(wt, power if small == "w" else 100).astype(np.float32))
+    ref = run_oracle(w, x, wt, np.zeros(w.K, np.float32), act=0, use_bias=False)
+    got, name = run_gpu(w, x, wt, None, act=0, use_bias=False, pin="tiled_f32_split_" + pin)
+    assert name == "tiled_f32_split_" + pin
+    err = np.linalg.norm(got - ref) / np.linalg.norm(ref)
+    print("%s %s 2^%d: %.2e" % (pin, small, power, err))
+    assert err < 1e-6, err
