@@ -1,0 +1,31 @@
+"""The kernel search of fp32 layers on the host, uncached as cvx_conv_fwd_query runs it: what a first call pays, and every call of a
+program with more problems than a handle keeps plans."""
+import ctypes
+import time
+
+import pytest
+
+import workloads as wl
+from paper_1910_00078_amd import cvx
+
+
+def _v(**kw):
+    return wl.small_variant(wl.WORKLOADS["c2"], dtype=wl.F32, **kw)
+
+
+@pytest.mark.parametrize("w,limit", [
+    # us with the call through ctypes, which is one of them; before each tile's shape was found directly and the search on the fp32 pipe
+    # left out where it cannot win: 2.9, 5.5, 3.8, 9.2 and 26 to 28
+    (_v(), 2.5), (_v(N=128, C=512, H=7, W=7, K=512), 3.0), (_v(N=1, C=8, H=8, W=8, K=8), 3.0), (_v(N=4096, C=512, H=2, W=2, K=512), 4.5),
+    (_v(N=4096, C=512, H=1, W=1, K=512), 25.0),
+], ids=lambda v: "%dx%d_%d" % (v.N, v.C, v.H) if hasattr(v, "N") else "")
+def test_fp32_search_is_cheap(w, limit):
+    L, buf, ws, best = cvx.lib(), ctypes.create_string_buffer(128), ctypes.c_ulonglong(), 1e9
+    with cvx.ConvPlan(cvx.CVX_F32, (w.N, w.C, w.H, w.W), (w.K, w.C, w.R, w.S), w.pad, w.stride, w.dil, w.groups) as plan:
+        for _ in range(60):                        # (the fastest of many short runs: a busy host slows a run, never speeds it)
+            t0 = time.perf_counter()
+            for _ in range(100):
+                L.cvx_conv_fwd_query(plan.xd, plan.wd, plan.cd, plan.yd, buf, 128, ctypes.byref(ws))
+            best = min(best, (time.perf_counter() - t0) / 100 * 1e6)
+    print("%.2f us" % best)
+    assert best < limit
