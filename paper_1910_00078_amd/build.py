@@ -8,15 +8,17 @@ hipcc cross-compiles without a GPU.  Objects and the shared library are written 
 from __future__ import annotations
 
 import os
+import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(CSRC, "_obj")
 LIB = os.path.join(HERE, "libcvx.so")
-TORCH_LIB = os.path.join(HERE, "_cvx_torch.so")
+TORCH_LIB = os.path.join(HERE, "_cvx_torch" + sysconfig.get_config_var("EXT_SUFFIX"))      # for this interpreter alone
 SOURCES = ["cvx_api.cpp", "kernels_direct.hip", "kernels_igemm.hip", "kernels_stem.hip", "kernels_pointwise.hip",
            "kernels_tiled_f32.hip", "kernels_split_f32.hip", "kernels_grouped.hip"]
 # Sources whose kernels are dealt over further objects (the same file with -DCVX_PART=1..n), so that a build uses the
@@ -91,21 +93,42 @@ def _build(force, verbose, defines, LIB, OBJ) -> str:
     return LIB
 
 
-def _build_torch(force, run, hdrs):
-    """The native one-call function on torch tensors (host code, compiled against the installed torch)."""
-    import sysconfig
+def _torch_prerequisites():
+    """What the native one-call function is compiled with -- torch, the C++ compiler -- or what of it is missing, as text."""
+    cxx = os.environ.get("CXX", "g++")
+    try:
+        import torch
+    except ImportError:
+        return "torch"
+    for header in (os.path.join(os.path.dirname(torch.__file__), "include", "ATen", "core", "Tensor.h"),
+                   os.path.join(sysconfig.get_paths()["include"], "Python.h")):
+        if not os.path.exists(header):
+            return header
+    return (torch, cxx) if shutil.which(cxx) else cxx
 
-    import torch
-    src, t = os.path.join(CSRC, "cvx_torch.cpp"), os.path.dirname(torch.__file__)
-    if not (force or _stale(TORCH_LIB, [src] + hdrs)):
+
+def _build_torch(force, run, hdrs, obj=OBJ):
+    """The native one-call function on torch tensors (host code, compiled against the installed torch, whose version it carries).  The C ABI
+    library does not need it, and conv_fwd_fused goes through that alone where it is missing."""
+    found = _torch_prerequisites()
+    if isinstance(found, str):
+        print("no native conv_fwd_fused: %s is missing" % found, file=sys.stderr)
+        return
+    torch, cxx = found
+    src, t, stamp = os.path.join(CSRC, "cvx_torch.cpp"), os.path.dirname(torch.__file__), os.path.join(obj, "_cvx_torch.version")
+    version = str(torch.__version__)
+    built_for = open(stamp).read() if os.path.exists(stamp) else ""
+    if not (force or built_for != version or _stale(TORCH_LIB, [src] + hdrs)):
         return
     tmp = TORCH_LIB + ".tmp%d" % os.getpid()
-    run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM",
+    run([cxx, "-O2", "-std=c++17", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-DUSE_ROCM", '-DCVX_TORCH_VERSION="%s"' % version,
          "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch.compiled_with_cxx11_abi(), "-I" + os.path.join(t, "include"),
          "-I" + os.path.join(t, "include", "torch", "csrc", "api", "include"), "-I/opt/rocm/include",
          "-I" + sysconfig.get_paths()["include"], src, "-o", tmp, "-L" + os.path.join(t, "lib"), "-ltorch_python", "-ltorch_cpu",
          "-lc10", "-lc10_hip", "-L" + HERE, "-l:" + os.path.basename(LIB), "-Wl,-rpath,$ORIGIN"])
     os.replace(tmp, TORCH_LIB)
+    with open(stamp, "w") as f:
+        f.write(version)
 
 
 if __name__ == "__main__":

@@ -136,4 +136,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_cvx_torch", nullptr, -1, methods,
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__cvx_torch() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__cvx_torch()
+{
+    PyObject* const m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "torch_version", CVX_TORCH_VERSION) != 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -336,16 +336,16 @@ class _PerThread(threading.local):
 _per_thread = _PerThread()
 
 
-_native = None      # the native one-call function, or False where it is not built
+_native = None      # the native one-call function, or False where it is not built or built for another torch
 
 
 def _load_native():
     global _native
-    import torch  # noqa: F401  (its libraries have to be there first)
+    import torch        # (its libraries have to be there first)
     lib()
     try:
         from . import _cvx_torch
-        _native = _cvx_torch.conv_fwd_fused
+        _native = _cvx_torch.conv_fwd_fused if getattr(_cvx_torch, "torch_version", None) == str(torch.__version__) else False
     except ImportError:
         _native = False
     return _native
