@@ -361,7 +361,9 @@ def conv_fwd_fused(x, w, bias=None, *, pad=0, stride=1, dil=1, groups=1, act=CVX
     if bn is None and out is None and pin is None and info is None and policy == 0 and type(policy) is int:
         # plain calls run natively (a tiny layer 8.05 -> 4.44 us, which the launch and the allocation of y are most of);
         # what that function does not take it leaves untouched, and the way below serves it or says what is wrong
-        native = _load_native() if _native is None else _native
+        native = _native
+        if native is None and x.is_cuda and w.is_cuda:
+            native = _load_native()
         if native:
             y = native(x, w, bias, pad, stride, dil, groups, act, alpha)
             if y is not None:

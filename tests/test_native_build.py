@@ -58,3 +58,14 @@ def test_one_of_another_torch_is_not_used(monkeypatch, version):
     monkeypatch.setattr(cvx, "_native", None)
     assert cvx._load_native() is (module.conv_fwd_fused if version == "ours" else False)
     assert os.path.basename(build.TORCH_LIB).startswith("_cvx_torch.cpython-")
+
+
+def test_cpu_tensors_are_refused_without_the_library(monkeypatch):
+    import torch
+
+    def no_library():
+        raise OSError("not built")
+    monkeypatch.setattr(cvx, "lib", no_library)
+    monkeypatch.setattr(cvx, "_native", None)
+    with pytest.raises(ValueError, match="GPU"):
+        cvx.conv_fwd_fused(torch.zeros(1, 8, 4, 4), torch.zeros(8, 8, 3, 3))
