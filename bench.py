@@ -31,7 +31,8 @@ sys.path.insert(0, ROOT)
 sys.path.insert(0, os.path.join(ROOT, "tests"))
 
 PEAK_MFMA_16BIT_TFLOPS = 2516.6      # dense bf16 / fp16 MFMA
-PEAK_FP32_TFLOPS = 157.3
+PEAK_FP32_TFLOPS = 157.3             # the fp32 matrix pipe, and the vector pipe
+PEAK_SPLIT_F32_TFLOPS = PEAK_MFMA_16BIT_TFLOPS / 6      # fp32 on the bf16 pipe: six products for one
 PEAK_HBM_GBS = 8000.0
 ROTATE_BYTES = 1 << 30               # rotate buffer sets over at least this much memory
 RESULTS_DIR = os.path.join(ROOT, "gpurun_out")   # where the per-layer tables are written as JSON
@@ -165,7 +166,7 @@ def measured_traffic(name):
     return None
 
 
-def roofline(w, name, ms_kernel):
+def roofline(w, name, kernel, ms_kernel):
     bound = BOUND[name]
     traffic = measured_traffic(name)
     src = "profiles/pmc_traffic.json (rocprofv3 FETCH_SIZE + WRITE_SIZE, scaled by a 256 MiB copy)" if traffic else None
@@ -174,8 +175,10 @@ def roofline(w, name, ms_kernel):
         return {"bound": "hbm", "achieved": ach, "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": ach / PEAK_HBM_GBS,
                 "traffic": traffic, "traffic_source": src}
     ach = w.flops / (ms_kernel * 1e-3) / 1e12
-    # a contraction is priced against the matrix peak of its own data type (fp32: 157.3, as the vector pipe)
-    peak = PEAK_MFMA_16BIT_TFLOPS if bound == "mfma" and w.dtype != "f32" else PEAK_FP32_TFLOPS
+    # a contraction is priced against the peak of the matrix pipe that its kernel runs on
+    peak = PEAK_FP32_TFLOPS
+    if bound == "mfma":
+        peak = PEAK_SPLIT_F32_TFLOPS if kernel.startswith("tiled_f32_split_") else PEAK_FP32_TFLOPS if w.dtype == "f32" else PEAK_MFMA_16BIT_TFLOPS
     return {"bound": bound, "achieved": ach, "peak": peak, "unit": "TFLOP/s", "frac": ach / peak, "traffic": traffic,
             "traffic_source": src}
 
@@ -209,7 +212,7 @@ def fusion_sweep(steps: int):
 def layer_row(name, rr):
     w = rr["workload"]
     ms = rr["event_ms_per_step"]
-    rf = roofline(w, name, ms)
+    rf = roofline(w, name, rr["kernel"], ms)
     return {"workload": name, "kernel": rr["kernel"], "us": ms * 1e3,
             "eager_us": None if rr["eager_ms_per_step"] is None else rr["eager_ms_per_step"] * 1e3,
             "tflops": w.flops / (ms * 1e-3) / 1e12, "gbs": w.algorithmic_bytes / (ms * 1e-3) / 1e9,
@@ -269,7 +272,7 @@ def main():
                                % (args.workload, w.dtype, w.N, w.C, w.H, w.W, w.K, w.R, w.S, w.pad[0], w.stride[0]),
                    "kernel": r["kernel"], "buffer_sets": r["nsets"],
                    "gflop_per_step": w.flops / 1e9, "algorithmic_mb_per_step": w.algorithmic_bytes / 1e6},
-        "roofline": roofline(w, args.workload, ms),
+        "roofline": roofline(w, args.workload, r["kernel"], ms),
         "cpu_baseline": r["cpu"],
         "parity": r["parity"],
         "event_ms_per_step": ms,

@@ -108,7 +108,7 @@ Command (run from the repository root on the GPU box, `TMPDIR=/tmp`):
 | %s | %d | %.3f | %.3f | %.3f | %.3f |
 
 bench.py in the same run (HIP events around the graph replays): %.3f us per step,
-%.1f %s = %.1f %% of the %s peak (%s %s).  Plain calls without a graph: %s us per step.
+%.1f %s = %.1f %% of the %s peak (%.1f %s).  Plain calls without a graph: %s us per step.
 
 Top kernels of the run (name, calls, total us, avg us, %% of GPU time):
 
