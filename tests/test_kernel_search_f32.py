@@ -9,23 +9,36 @@ import workloads as wl
 from paper_1910_00078_amd import cvx
 
 
+SCALE = 15.0
+
+
 def _v(**kw):
     return wl.small_variant(wl.WORKLOADS["c2"], dtype=wl.F32, **kw)
 
 
+@pytest.fixture(scope="module")
+def search():
+    L, buf, ws = cvx.lib(), ctypes.create_string_buffer(128), ctypes.c_ulonglong()
+
+    def us(plan, n):
+        t0 = time.perf_counter()
+        for _ in range(n):
+            L.cvx_conv_fwd_query(plan.xd, plan.wd, plan.cd, plan.yd, buf, 128, ctypes.byref(ws))
+        return (time.perf_counter() - t0) / n * 1e6
+    return us
+
+
 @pytest.mark.parametrize("w,limit", [
-    # us with the call through ctypes, which is one of them; before each tile's shape was found directly and the search on the fp32 pipe
-    # left out where it cannot win: 2.9, 5.5, 3.8, 9.2 and 26 to 28
+    # us on the host where a 16-bit search of the last layer takes SCALE, with the call through ctypes, which is one of them; before each
+    # tile's shape was found directly and the search on the fp32 pipe left out where it cannot win: 2.9, 5.5, 3.8, 9.2 and 26 to 28
     (_v(), 2.5), (_v(N=128, C=512, H=7, W=7, K=512), 3.0), (_v(N=1, C=8, H=8, W=8, K=8), 3.0), (_v(N=4096, C=512, H=2, W=2, K=512), 4.5),
     (_v(N=4096, C=512, H=1, W=1, K=512), 25.0),
 ], ids=lambda v: "%dx%d_%d" % (v.N, v.C, v.H) if hasattr(v, "N") else "")
-def test_fp32_search_is_cheap(w, limit):
-    L, buf, ws, best = cvx.lib(), ctypes.create_string_buffer(128), ctypes.c_ulonglong(), 1e9
-    with cvx.ConvPlan(cvx.CVX_F32, (w.N, w.C, w.H, w.W), (w.K, w.C, w.R, w.S), w.pad, w.stride, w.dil, w.groups) as plan:
+def test_fp32_search_is_cheap(search, w, limit):
+    shape = (w.N, w.C, w.H, w.W), (w.K, w.C, w.R, w.S), w.pad
+    ours = scale = 1e9
+    with cvx.ConvPlan(cvx.CVX_F32, *shape) as plan, cvx.ConvPlan(cvx.CVX_BF16, (4096, 512, 1, 1), (512, 512, 3, 3), 1) as other:
         for _ in range(60):                        # (the fastest of many short runs: a busy host slows a run, never speeds it)
-            t0 = time.perf_counter()
-            for _ in range(100):
-                L.cvx_conv_fwd_query(plan.xd, plan.wd, plan.cd, plan.yd, buf, 128, ctypes.byref(ws))
-            best = min(best, (time.perf_counter() - t0) / 100 * 1e6)
-    print("%.2f us" % best)
-    assert best < limit
+            ours, scale = min(ours, search(plan, 100)), min(scale, search(other, 20))
+    print("%.2f us, 16-bit search %.2f" % (ours, scale))
+    assert ours < limit * scale / SCALE
