@@ -99,7 +99,9 @@ __device__ __forceinline__ float finish(float acc, const ChannelAffine& ca, bool
 // The bias + ReLU (or identity) epilogue on values already rounded to bf16 / fp16 and packed two to
 // a dword.  Both formats are sign-magnitude, so as signed 16-bit integers the negative values are
 // exactly the negative integers: max(v, 0) is ReLU, max(v, -32768) the identity, one v_pk_max_i16 for
-// two values.  Rounding before the ReLU gives the same result as after it (rounding keeps the sign).
+// two values.  Rounding before the ReLU gives the same result as after it (rounding keeps the sign).  A NaN
+// becomes 0, as by fmaxf, if it is negative: those that the matrix instruction and v_fma make are, and the ones of a
+// batch-norm array are made so (negative_nans).
 typedef short s16x2_t __attribute__((ext_vector_type(2)));
 __device__ __forceinline__ uint32_t packed_floor(bool relu)
 {
@@ -108,6 +110,12 @@ __device__ __forceinline__ uint32_t packed_floor(bool relu)
 __device__ __forceinline__ uint32_t max_packed(uint32_t v, uint32_t floor2)
 {
     return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(s16x2_t, v), __builtin_bit_cast(s16x2_t, floor2)));
+}
+
+__device__ __forceinline__ ChannelAffine negative_nans(const ChannelAffine& ca)
+{
+    const auto negative = [](uint32_t v) __attribute__((always_inline)) { return __uint_as_float((v & 0x7fffffffu) > 0x7f800000u ? v | 0x80000000u : v); };
+    return {negative(__float_as_uint(ca.mul)), negative(__float_as_uint(ca.add))};
 }
 
 // ---- vector types, the 16-bit matrix instruction and the packed output conversion, shared by the MFMA kernels
@@ -155,7 +163,8 @@ __device__ __forceinline__ void with_epilogue(const ConvArgs& a, bool has_bn, Ru
         run([=](float v0, float v1, const ChannelAffine&) __attribute__((always_inline)) { return max_packed(pack2<DT>(v0, v1), floor2); });
     } else if (packed) {
         run([=](float v0, float v1, const ChannelAffine& ca) __attribute__((always_inline)) {
-            return max_packed(pack2<DT>(fmaf(v0, ca.mul, ca.add), fmaf(v1, ca.mul, ca.add)), floor2);
+            const ChannelAffine c = negative_nans(ca);         // (once a filter: the loops over its values are unrolled)
+            return max_packed(pack2<DT>(fmaf(v0, c.mul, c.add), fmaf(v1, c.mul, c.add)), floor2);
         });
     } else if (a.act == ACT_LEAKY_RELU) {
         run([=](float v0, float v1, const ChannelAffine& ca) __attribute__((always_inline)) {

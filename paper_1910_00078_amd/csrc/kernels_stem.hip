@@ -598,10 +598,11 @@ __global__ void __launch_bounds__(STREAM_THREADS) stem_stream_kernel(ConvArgs a,
 #pragma unroll
                 for (int tn = 0; tn < TN; ++tn) {
                     if (packed_act && has_bn) {
+                        const ChannelAffine c = negative_nans(ca[tn]);
 #pragma unroll
                         for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
-                            for (int r = 0; r < 16; ++r) acc[tm][tn][r] = fmaf(acc[tm][tn][r], ca[tn].mul, ca[tn].add);
+                            for (int r = 0; r < 16; ++r) acc[tm][tn][r] = fmaf(acc[tm][tn][r], c.mul, c.add);
                     }
                     if (packed_act) {
                         // bias + ReLU / identity: round, then ReLU on the packed pair, 1 instruction per value

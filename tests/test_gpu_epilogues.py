@@ -49,3 +49,28 @@ def test_stem_tile_heights(pin, rows, size):
     assert name == pin
     ok, msg = tolerance_ok(got, run_oracle(w, x, wt, b), w.dtype)
     assert ok, msg
+
+
+@pytest.mark.parametrize("bn", [False, True], ids=["bias", "bn"])
+@pytest.mark.parametrize("dtype", [wl.BF16, wl.F16])
+@pytest.mark.parametrize("w,pin", LAYERS + [(wl.small_variant(_c4, N=1, H=24, W=24), "stem_128x64_k11")], ids=[p for _, p in LAYERS] + ["stem_128x64_k11"])
+def test_relu_of_nan_and_infinity(w, pin, dtype, bn):
+    """ReLU makes 0 of a NaN of either sign, be it from x, from the bias or from the batch-norm arrays, in the direct kernel and in
+    these; and infinities come out as the direct kernel's."""
+    w = wl.small_variant(w, dtype=dtype)
+    (x, wt, b), (nan, inf) = wl.make_inputs(w), {wl.BF16: (0x7fc0, 0x7f80), wl.F16: (0x7e00, 0x7c00)}[dtype]
+    x, b, rng = x.copy(), b.copy(), np.random.default_rng(7)
+    stats = [rng.uniform(lo, hi, w.K).astype(np.float32) for lo, hi in ((-1.5, 1.5), (-0.5, 0.5), (-0.3, 0.3), (0.5, 2.0))] if bn else None
+    b.view(np.uint16)[[1, 4]] = nan, nan | 0x8000
+    if bn:
+        stats[0][3], stats[2][5] = np.nan, -np.nan
+    for first in (nan, inf) if w.R < 7 else (None,):        # (the stem's zero weights past its filter meet what lies there)
+        if first:
+            x.view(np.uint16)[0, 1, 1, 1], x.view(np.uint16)[-1, 2, 5, 6] = first, first | 0x8000
+        got, name = run_gpu(w, x, wt, b, bn=stats, pin=pin)
+        want, _ = run_gpu(w, x, wt, b, bn=stats, policy=1)
+        assert name == pin and not np.isnan(want).any() and np.all(want[:, 1] == 0.0)
+        np.testing.assert_array_equal(np.isinf(got), np.isinf(want))
+        got[np.isinf(got)] = want[np.isinf(want)] = 0.0
+        ok, msg = tolerance_ok(got, want, dtype)
+        assert ok, msg
