@@ -1458,8 +1458,9 @@ bool igemm_plan(const ConvArgs& a, const PlanEnv& env, LaunchPlan* out)
         }
     }
     if (!bv && !uv) return false;
-    // The fitted estimate overrules the relative one where it sees more than its own uncertainty between the two choices: over
-    // 413 layers 1.09x faster, one of them more than 3 % slower (without the margin eleven).
+    // The fitted estimate overrules the relative one where it sees more than 5 % between the two choices.  That is half of its own
+    // error for a layer (8 to 13 %); the line lies where 413 layers had it: 1.09x faster, one of them more than 3 % slower, eleven
+    // without a margin.
     if (!only && uv && uv != bv) {
         const Fit* f = bv ? fit_of((int)(bv - kVariants)) : nullptr;
         if (!bv || (f && best_us < 0.95 * estimate(*bv, *f, bg, env.cus))) {
